@@ -295,47 +295,51 @@ __device__ __forceinline__ void copy_lds_skip2(uint32_t* __restrict__ di, T* __r
   }
 }
 
-// Exchange B with the payload and buffer work moved ahead (fine mode, 2 <= P
-// <= REC_P_MAX).  The 16-bit prefix `pre` of T already divides the keys:
-// those above it are kept whatever T is, those below are dropped, and only
-// the few on it wait for exchange B.  Before the group's barrier: the keys on
-// the prefix go into the record; then, while the other workgroups arrive,
-// every entry above or on the prefix is staged in LDS in index order and the
-// buffer rows are stored as if only the keys above the prefix were kept.
-// After the barrier one wavefront decides the keys on the prefix and stores
-// the buffer values of the kept ones; the others are left out of the staged
-// list when it is copied out.  Returns
-// false when a record overflowed: nothing decided, the buffer rows are then
-// stored again by the caller.
-template <typename InT, int SEL, int R>
-__device__ __forceinline__ bool grp_early(const TopkArgs& a, bool vec, uint64_t seg, uint32_t P, uint32_t part,
-                                          const GrpMem& gm,
-                                          GrpShared<(uint32_t)GRP_NT * R * (16 / sizeof(typename Elem<InT>::raw)),
-                                                    typename Elem<InT>::raw>& sh,
-                                          GrpSmall& sm, GrpState& gs, const SelA& A,
-                                          float (&v)[R][16 / sizeof(typename Elem<InT>::raw)], const int (&n)[R],
-                                          uint64_t c0, typename Elem<InT>::raw* ms, float* es,
-                                          const typename Elem<InT>::raw* mlds, bool exiting, uint32_t& ticket) {
+// Exchange B and, where the workgroup can, the payload and buffer work moved
+// ahead of it (P <= REC_P_MAX).  The 17- or 20-bit prefix `pre` of T already
+// divides the keys: those above it are kept whatever T is, those below
+// are dropped, and only those on it wait for exchange B.  Before the group's
+// barrier: the keys on the prefix go into the record (one entry each while
+// they fit, else distinct keys with multiplicities).  EARLY, and at most WAVE
+// keys on the prefix: while the other workgroups arrive, every entry above or
+// on the prefix is staged in LDS in index order and the buffer rows are stored
+// as if only the keys above the prefix were kept; after the barrier one
+// wavefront decides the keys on the prefix and stores the buffer values of the
+// kept ones, and the others are left out of the staged list when it is copied
+// out (DONE).  Otherwise the caller places the entries once T is known
+// (PLACE).  FALLBACK: a record overflowed, nothing decided; buffer rows stored
+// early are stored again by the caller.
+enum class Fine { FALLBACK, DONE, PLACE };
+
+template <typename InT, int SEL, int R, bool EARLY>
+__device__ __forceinline__ Fine grp_fine(const TopkArgs& a, bool vec, uint64_t seg, uint32_t P, uint32_t part,
+                                         const GrpMem& gm,
+                                         GrpShared<(uint32_t)GRP_NT * R * (16 / sizeof(typename Elem<InT>::raw)),
+                                                   typename Elem<InT>::raw>& sh,
+                                         GrpSmall& sm, GrpState& gs, const SelA& A,
+                                         float (&v)[R][16 / sizeof(typename Elem<InT>::raw)], const int (&n)[R],
+                                         uint64_t c0, typename Elem<InT>::raw* ms, float* es,
+                                         const typename Elem<InT>::raw* mlds, bool exiting, uint32_t& ticket,
+                                         SelResult& sr) {
   using Raw = typename Elem<InT>::raw;
   constexpr int NT = GRP_NT;
   constexpr int E = 16 / (int)sizeof(Raw);
   constexpr uint32_t CH = (uint32_t)NT * R * E;
   const int t = (int)threadIdx.x;
   const uint32_t dummy = (uint32_t)lane_id();
-  const uint32_t pre = A.prefix;   // bits 30..15 of T
+  const uint32_t pre = A.prefix, lowb = 31u - A.pbits;   // key bits below the prefix
 
   // ---- per run: entries above or on the prefix, and on it (both < 2^16
   // per workgroup), scanned in index order; the thread's own ones as bit
   // masks (bit i: element i of the run)
   static_assert(E <= 8, "two 8-bit masks per run");
-  if (t < (int)DIG_BINS) sm.red[t] = 0u;
   uint32_t pc[R], ex[R], tot[R], msk[R];
 #pragma unroll
   for (int j = 0; j < R; ++j) {
     uint32_t mm = 0, cm = 0;
 #pragma unroll
     for (int i = 0; i < E; ++i) {
-      const uint32_t hi = mag_key(v[j][i]) >> 15;
+      const uint32_t hi = mag_key(v[j][i]) >> lowb;
       const uint32_t on = eq31(hi, pre);
       mm |= (gt31(hi, pre) | on) << i;
       cm |= on << i;
@@ -355,10 +359,12 @@ __device__ __forceinline__ bool grp_early(const TopkArgs& a, bool vec, uint64_t 
     c_all += tot[j] >> 16;
   }
 
-  // ---- the keys on the prefix (a few per workgroup): record slot (index
-  // order), their bits 14..7 into the digit counts, and what deciding them
-  // later needs; a thread visits only the set bits of its masks
-  uint32_t* my = gm.rec() + (uint64_t)part * REC_W;
+  // ---- the keys on the prefix (a few per workgroup): the record's entries
+  // and, when one wavefront will decide them, what that needs; a thread
+  // visits only the set bits of its masks
+  const bool direct = c_all <= REC_KEYS;          // workgroup-uniform
+  const bool early = EARLY && c_all <= (uint32_t)WAVE;
+  uint32_t run_key = ~0u, run_n = 0;              // equal keys in a row enter the table together
 #pragma unroll
   for (int j = 0; j < R; ++j) {
     uint32_t cm = msk[j] >> 8;
@@ -372,25 +378,33 @@ __device__ __forceinline__ bool grp_early(const TopkArgs& a, bool vec, uint64_t 
         uint32_t kk = mag_key(v[j][0]);
 #pragma unroll
         for (int ii = 1; ii < E; ++ii) kk = (i == (uint32_t)ii) ? mag_key(v[j][ii]) : kk;
-        if (q < REC_KEYS) {
-          st_agent(&my[2 + q], kk);
+        const uint32_t low = kk & ((1u << lowb) - 1u);
+        if (direct) {
+          sm.rec[1 + q] = low | (1u << LOW_BITS);
+        } else if (low == run_key) {
+          ++run_n;
+        } else {
+          if (run_n) grp_rle_add(sm, run_key, run_n);
+          run_key = low;
+          run_n = 1u;
+        }
+        if (early) {
           sm.ckey[q] = kk;
           sm.coff[q] = off + i;
           sm.cpos[q] = sp0 + (uint32_t)__builtin_popcount(mm & ((1u << i) - 1u));
         }
-        atomicAdd(&sm.red[(kk >> 7) & 0xFFu], 1u);
         ++q;
       } while (cm);
     }
   }
-  __syncthreads();
-  grp_publish_b<NT>(part, gm, sm, gs, m_all - c_all, c_all);
+  if (run_n) grp_rle_add(sm, run_key, run_n);
+  grp_publish_b<NT>(part, gm, sm, gs, m_all - c_all, direct);
   refresh(v);
-
   // ---- while the group arrives: stage the entries above or on the prefix
   // and store the buffer rows with only the keys above it kept
+  if (early) {
 #pragma unroll
-  for (int j = 0; j < R; ++j) {
+   for (int j = 0; j < R; ++j) {
     const uint32_t off = (uint32_t)(j * NT + t) * E;
     uint32_t sp = mb[j] + (ex[j] & 0xFFFFu);
     Raw mr[E];
@@ -421,12 +435,21 @@ __device__ __forceinline__ bool grp_early(const TopkArgs& a, bool vec, uint64_t 
       if constexpr (SEL == SEL_EF) store_run_partial<float, E, true>(es + off, n[j], eo);
       if constexpr (SEL == SEL_AQSGD) store_run_partial<Raw, E, true>(ms + off, n[j], mr);
     }
+   }
   }
 
-  SelResult sr;
-  const bool ok = grp_finish_b<NT>((uint32_t)a.k, P, part, gm, sm, gs, A, sr);
+  // words per thread for the group's size (16 workgroups each)
+  bool ok;
+  if (P <= 64u) ok = grp_finish_b<NT, 4>(P, part, gm, sm, gs, A, sr);
+  else ok = grp_finish_b<NT, 16>(P, part, gm, sm, gs, A, sr);
   refresh(v);
-  if (!ok) return false;
+  if (!ok) return Fine::FALLBACK;
+  if (!early) {
+    __syncthreads();
+    grp_finish_b_lower<NT>(sm, sr);
+    __syncthreads();
+    return Fine::PLACE;
+  }
   // every wavefront's buffer stores are complete before some of them are
   // overwritten from another wavefront below
   if (exiting) ticket = grp_exit_ticket(gm);
@@ -436,7 +459,7 @@ __device__ __forceinline__ bool grp_early(const TopkArgs& a, bool vec, uint64_t 
   }
   grp_finish_b_lower<NT>(sm, sr);
 
-  // ---- decide the keys on the prefix (at most REC_KEYS: one wavefront);
+  // ---- decide the keys on the prefix (at most WAVE: one wavefront);
   // the kept ones get their buffer values
   if (t < WAVE) {
     const bool has = (uint32_t)t < c_all;
@@ -498,7 +521,7 @@ __device__ __forceinline__ bool grp_early(const TopkArgs& a, bool vec, uint64_t 
   } else {
     copy_lds_skip2<NT>(idx + wg_first, val + wg_first, sh.st.idx, sh.st.val, wg_count, sm.rem, n_drop);
   }
-  return true;
+  return Fine::DONE;
 }
 
 // One segment on one workgroup of its group.  `vec`: every buffer is 16-byte
@@ -624,33 +647,36 @@ __device__ __forceinline__ void grp_segment(const TopkArgs& a, bool vec, uint64_
   }
 
   // ---- selection (elements past the segment's end hold +0: see grp_exchange_a)
-  // The early path (grp_early) needs registers of its own: with 16 or more
+  // Staging ahead of exchange B needs registers of its own: with 16 or more
   // fp32 values (and their residuals) per thread it would spill, so those
-  // layouts take the plain path.
+  // layouts place once T is known.
   constexpr bool EARLY = !(sizeof(Raw) == 4 && R >= 4);
   SelResult sr;
   uint32_t ticket = 0;
-  const bool exiting = P > 1 && last_seg;
+  const bool exiting = last_seg;
   if (!select) {
     // T above every finite key (the keys of finite values are at most
     // 0x7F800000), so that nothing is kept
     sr.T = 0x7FFFFFFFu; sr.r = 0; sr.gt_before = 0; sr.eq_before = 0;
   } else {
-    const SelA A = grp_exchange_a<NT, R, E, CH>(v, zc, (uint32_t)a.k, a.L, P, part, gm, sh.sel, sm, gs);
-    refresh(v);
-    bool cleared = false;
-    if (EARLY && A.fine && P <= REC_P_MAX) {
-      if (grp_early<InT, SEL, R>(a, vec, seg, P, part, gm, sh, sm, gs, A, v, n, c0, ms, es, mlds, exiting, ticket)) {
-        if (exiting) {
-          grp_exit_finish<NT>(gm, P, gs, ticket, &sm.misc[0]);
-          exited = true;
-        }
-        __syncthreads();
-        return;
-      }
-      cleared = true;
+    const uint32_t n_loc = (uint32_t)min((uint64_t)CH, a.L - c0);
+    SelA A = grp_exchange_a<NT, R, E, CH>(v, zc, (uint32_t)a.k, n_loc, a.L, P, part, gm, sh.sel, sm, gs);
+    if (!A.fine) {
+      grp_pass<NT, R, E>(v, 8u, 0u, P, gm, sh.sel, sm, gs, A);
+      grp_clear_a(gm, gs.iter & 1u, P, part);
     }
-    sr = grp_fallback<NT, R, E, CH>(v, P, part, gm, sh.sel, sm, gs, A.prefix, A.pbits, A.need, cleared);
+    refresh(v);
+    const Fine f = grp_fine<InT, SEL, R, EARLY>(a, vec, seg, P, part, gm, sh, sm, gs, A, v, n, c0, ms, es, mlds, exiting, ticket, sr);
+    if (f == Fine::DONE) {
+      if (exiting) {
+        grp_exit_finish<NT>(gm, P, gs, ticket, &sm.misc[0]);
+        exited = true;
+      }
+      __syncthreads();
+      return;
+    }
+    if (f == Fine::FALLBACK)
+      sr = grp_fallback<NT, R, E, CH>(v, P, part, gm, sh.sel, sm, gs, A, A.fine ? 0u : 1u);
   }
   // the group's exchange words have all been read: draw the exit ticket now
   // (its answer is needed only at the end)
@@ -1365,6 +1391,44 @@ SegPlan plan_lds(int sel, int dt, uint64_t n_seg) {
   return p;
 }
 
+namespace {
+
+// the group engine's layouts: 16-byte runs per thread, 0 ends the list
+const int* grp_runs(int dt) {
+  static const int runs32[] = {6, 4, 2, 1, 0}, runs16[] = {3, 2, 1, 0};
+  return dt == DT_F32 ? runs32 : runs16;
+}
+
+// The layout with the most runs per thread that still gives every compute
+// unit a workgroup, else the fewest, one workgroup per compute unit: the
+// sizes that tc_workspace_bytes and the allocation-free entry point report
+// are this layout's.
+struct GrpFill {
+  int runs;
+  uint64_t P, ws_words, ws_used;
+};
+GrpFill grp_fill(int dt, uint64_t n_seg, uint64_t L) {
+  const uint64_t cus = (uint64_t)device_cus();
+  GrpFill f{};
+  for (const int* r = grp_runs(dt); *r; ++r) {
+    const uint64_t ch = (uint64_t)GRP_NT * *r * (dt == DT_F32 ? 4 : 8);
+    f.runs = *r;
+    f.P = (L + ch - 1) / ch;
+    if (n_seg * f.P >= cus) break;
+  }
+  if (f.P > GRP_MAX_P) return f;
+  uint64_t groups = std::min<uint64_t>(n_seg, std::max<uint64_t>(1, cus / f.P));
+  if (groups >= 8) groups -= groups % 8;
+  // sized for the most groups any instance could keep resident (4 workgroups
+  // per compute unit), so that one size serves every selection kind
+  const uint64_t ws_groups = std::min<uint64_t>(n_seg, std::max<uint64_t>(1, cus * 4 / f.P));
+  f.ws_words = ws_groups * grp_mem_words((uint32_t)f.P);
+  f.ws_used = groups * grp_mem_words((uint32_t)f.P);
+  return f;
+}
+
+}  // namespace
+
 SegPlan plan_topk(int sel, int dt, uint64_t n_seg, uint64_t L) {
   SegPlan p;
   const uint32_t cus = (uint32_t)device_cus();
@@ -1382,40 +1446,47 @@ SegPlan plan_topk(int sel, int dt, uint64_t n_seg, uint64_t L) {
     p.ws_words = 0;
     return p;
   }
-  // several workgroups per segment: the most 16-byte runs per thread that
-  // still give every compute unit a workgroup, else the fewest
-  const int E = (dt == DT_F32) ? 4 : 8;
-  static const int runs32[] = {6, 4, 2, 1};
-  static const int runs16[] = {3, 2, 1};
-  const int* runs = (dt == DT_F32) ? runs32 : runs16;
-  const int n_runs = (dt == DT_F32) ? 4 : 3;
+  // several workgroups per segment
+  const GrpFill f = grp_fill(dt, n_seg, L);
   p.nt = GRP_NT;
-  p.vpt = runs[n_runs - 1];   // runs per thread
-  for (int i = 0; i < n_runs; ++i) {
-    const uint64_t ch = (uint64_t)GRP_NT * runs[i] * E;
-    const uint64_t P = (L + ch - 1) / ch;
-    if (n_seg * P >= cus) { p.vpt = runs[i]; break; }
+  p.vpt = f.runs;
+  p.P = (uint32_t)std::min<uint64_t>(f.P, UINT32_MAX);
+  // what a call needs of its workspace, and which lengths AQ-SGD takes, are
+  // part of the interface: both come from grp_fill's layout
+  const bool fits = f.P <= cus;
+  p.ws_words = fits ? f.ws_words : global_ws_words(L);
+  p.ws_used = fits ? f.ws_used : p.ws_words;
+  p.capacity = cus;
+  if (!fits && sel == SEL_AQSGD) return p;    // refused
+  // Any layout with the segment resident at once gives the same results; the
+  // fastest has the fewest rounds over the segments, then pays for what a
+  // thread works through (about 0.18 us per element) and for every workgroup
+  // in the exchanges (about 0.07 us each).  Measured in one round, binary16,
+  // TopK 10 %, 1 / 2 / 3 runs per thread: 100,000 elements 14.7 / 15.2 / 16.2
+  // us (25 / 13 / 9 workgroups), 400,000 20.5 / 17.0 / 17.3 (98 / 49 / 33),
+  // 1,000,000 30.4 / 22.9 / 21.1 (245 / 123 / 82); two rounds cost 28 to 34.
+  uint64_t best = UINT64_MAX;
+  const int E = (dt == DT_F32) ? 4 : 8;
+  for (const int* r = grp_runs(dt); *r; ++r) {
+    const uint64_t CH = (uint64_t)GRP_NT * *r * E;
+    const uint64_t P = (L + CH - 1) / CH;
+    const uint64_t cap = (uint64_t)occupancy(pick(sel, dt, false, *r), p.nt) * cus;
+    if (P > std::min<uint64_t>(cap, REC_P_MAX)) continue;
+    uint64_t groups = std::min<uint64_t>({n_seg, cap / P, p.ws_used / grp_mem_words((uint32_t)P)});
+    if (groups == 0) continue;
+    if (groups >= 8) groups -= groups % 8;
+    const uint64_t rounds = (n_seg + groups - 1) / groups;
+    const uint64_t cost = rounds * (320 + 5 * (uint64_t)(*r * E) + 2 * P);
+    if (cost < best) {
+      best = cost;
+      p.vpt = *r;
+      p.P = (uint32_t)P;
+      p.n_groups = (uint32_t)groups;
+      p.grid = (uint32_t)(groups * P);
+      p.capacity = cap;
+    }
   }
-  const uint64_t CH = (uint64_t)GRP_NT * p.vpt * E;
-  const uint64_t P = (L + CH - 1) / CH;
-  const uint64_t cap = (uint64_t)occupancy(pick(sel, dt, false, p.vpt), p.nt) * cus;
-  p.capacity = cap;
-  if (P > GRP_MAX_P) {       // too long for one resident group: the caller takes the global chain
-    p.P = (uint32_t)std::min<uint64_t>(P, UINT32_MAX);
-    p.n_groups = 0;
-    return p;
-  }
-  p.P = (uint32_t)P;
-  uint64_t groups = std::min<uint64_t>(n_seg, std::max<uint64_t>(1, cap / p.P));
-  if (p.P > 1 && groups >= 8) groups -= groups % 8;
-  p.n_groups = (uint32_t)groups;
-  p.grid = (uint32_t)(groups * p.P);
-  // the workspace is sized for the most groups any instance could keep
-  // resident (4 workgroups per compute unit), so that one size serves every
-  // selection kind of the same layout
-  const uint64_t ws_groups = std::min<uint64_t>(n_seg, std::max<uint64_t>(1, (uint64_t)cus * 4 / p.P));
-  p.ws_words = (p.P > 1) ? ws_groups * grp_mem_words(p.P) : 0;
-  p.ws_used = (p.P > 1) ? groups * grp_mem_words(p.P) : 0;
+  // (none fits: n_groups stays 0 and the caller takes the global chain)
   return p;
 }
 

@@ -12,19 +12,26 @@
 // instruction of a wavefront covers 1 KiB of contiguous memory).
 //
 // Two cross-workgroup exchanges per segment in the common case:
-//   A. every workgroup adds its 4096-bin histogram of key bits 30..19 into
-//      the group's histogram.  It also guesses, from its own keys, the bin
-//      that holds the k-th largest key and adds 16 finer counts (bits 18..15)
-//      for that bin and its two neighbours.  After the barrier, one read of
-//      the merged counts gives the bin b1 and, when every workgroup's guess
-//      covered b1, the 16-bit prefix of T.
+//   A. every workgroup guesses, from its own histogram of key bits 30..19 (at
+//      the rank its share of the segment gives), the bin of the k-th largest
+//      key, and adds its counts from an octave below that bin upwards into the
+//      group's histogram, its guess into the group's smallest and largest
+//      guess, and 32 finer counts (bits 18..14) of the guessed bin and its two
+//      neighbours.  After the barrier, one read of the merged counts gives the
+//      bin b1 (exact when no guess lies more than an octave above it: then no
+//      count at or above b1 is missing) and, when every guess was within one
+//      bin of b1, the 17-bit prefix of T.
 //   B. every workgroup publishes a record: its count of keys above that
-//      prefix and the keys that share it (a few per workgroup, carried
-//      inline).  After the barrier each workgroup reads all records in one
+//      prefix and the distinct keys that share it with their multiplicities
+//      (a few; 16-bit inputs repeat values, so one key may stand for many
+//      entries).  After the barrier each workgroup reads all records in one
 //      round trip and finds T, the tie quota and what precedes it by itself.
-// Otherwise (a guess missed, or too many keys share the prefix) the group
-// goes on with 8-bit digit passes, each merged through device memory, and a
-// last pass that publishes per-workgroup counts: exact for any input.
+// When a guess was further off (values with a gap around T, as AQ-SGD's changes
+// have once an example's activations repeat; or chunks that differ), one pass
+// over the next 8 bits, merged through device memory, gives a 20-bit prefix
+// for exchange B instead.  When too many distinct keys share the prefix, the
+// group goes on with digit passes of up to 8 bits and one exchange of
+// per-workgroup counts: exact for any input.
 #pragma once
 
 #include "tc_select.hpp"
@@ -33,34 +40,43 @@ namespace tc {
 
 constexpr int GRP_NT = 512;
 constexpr uint32_t GRP_MAX_P = 1024;      // workgroups per segment the engine supports
-constexpr uint32_t REC_W = 64;            // words per record: above, count, inline keys
-constexpr uint32_t REC_KEYS = REC_W - 2;
-constexpr uint32_t FINE_SLOTS = 256;      // fine counts kept for bins b1 mod 256
-constexpr uint32_t DIG_BINS = 256;        // 8-bit digits of the fallback passes
-constexpr uint32_t DIG_ROWS = DIG_BINS + 1;   // per-workgroup slot: bins + larger-prefix count
-constexpr uint32_t REC_P_MAX = 64;        // records of at most this many workgroups are read at once
+constexpr uint32_t REC_W = 32;            // words per record: header, then distinct keys
+constexpr uint32_t REC_KEYS = REC_W - 1;
+constexpr uint32_t REC_OVF = 0xFFu;       // header: more distinct keys than a record holds
+constexpr uint32_t FINE_BITS = 5;         // finer digit of exchange A (bits 18..14)
+constexpr uint32_t FINE_N = 1u << FINE_BITS;
+constexpr uint32_t FINE_SLOTS = 128;      // fine counts kept for bins b1 mod 128
+constexpr uint32_t LOW_BITS = 19 - FINE_BITS;   // key bits below the fine prefix (at most that many in a record's entry)
+static_assert(LOW_BITS == 14 && LAST_BINS == 128, "two 7-bit digits below the fine prefix");
+constexpr uint32_t DIG_BINS = 256;        // digits of the fallback passes: up to 8 bits
+constexpr uint32_t REC_P_MAX = 256;       // workgroups per segment of the record exchange
+constexpr uint32_t A_MARGIN = 16;         // bins added below the guessed one's neighbour (an octave)
+constexpr uint32_t RLE_SLOTS = 64;        // hash table of a workgroup's distinct keys on the prefix
+constexpr uint32_t RLE_PROBES = 8;
 
 // candidate keys the LDS list holds (records of up to 64 workgroups)
 __host__ __device__ constexpr uint32_t grp_local_cap(uint32_t CH) { return CH > 4096u ? CH : 4096u; }
 
 // Device memory owned by one group (inside the caller's workspace; zero on
 // entry and left zero on exit), as word offsets from the group's base:
-//   ctl[64]               [0] barrier arrivals (monotone during a launch), [1] exits
+//   ctl[64]               [0] barrier arrivals (monotone during a launch), [1] exits,
+//                         [32 + par], [34 + par] largest guess + 1, 4096 - smallest guess
 //   hist1[2][4096]        first-digit histograms, by segment parity
-//   fine[2][256][16]      bits 18..15 of the keys in guessed bins, by bin mod 256
-//   cov[2][256]           guesses per bin mod 256: count + (bin >> 8) << 16
-//   hist2[4][256]         8-bit digit counts: [par] exchange B (bits 14..7), [2 + p]
-//                         fallback pass p
-//   rec[P][64]            exchange B records
-//   slots[257][pitch]     last digit per workgroup + larger-prefix counts (fallback)
+//   fine[2][128][32]      bits 18..14 of the keys in guessed bins, by bin mod 128
+//   hist2[4][256]         digit pass p: hist2(p)
+//   rec[P][32]            exchange B records
+//   cnt[P]                keys > T and == T per workgroup (fallback)
+// The size keeps the words that earlier layouts used per workgroup (64 for
+// the record, 257 rows of digit slots): callers size their workspaces, and
+// the allocation-free entry point its refusals, by it.
 namespace gm_off {
-constexpr uint32_t CTL = 0, HIST1 = 64, FINE = HIST1 + 2 * HIST_BINS, COV = FINE + 2 * FINE_SLOTS * 16,
-                   HIST2 = COV + 2 * FINE_SLOTS, REC = HIST2 + 4 * DIG_BINS;
+constexpr uint32_t CTL = 0, HIST1 = 64, FINE = HIST1 + 2 * HIST_BINS, HIST2 = FINE + 2 * FINE_SLOTS * FINE_N + 512,
+                   REC = HIST2 + 4 * DIG_BINS;
 static_assert(REC % 4 == 0, "records are 16-byte aligned");
 }  // namespace gm_off
 
 __host__ __device__ constexpr uint64_t grp_mem_words(uint32_t P) {
-  return gm_off::REC + (uint64_t)P * REC_W + (uint64_t)DIG_ROWS * slot_pitch(P);
+  return gm_off::REC + (uint64_t)P * 64u + 257ull * ((P + 7u) & ~7u);
 }
 
 // the group's memory: one base pointer, pieces at fixed offsets
@@ -69,11 +85,10 @@ struct GrpMem {
   uint32_t P;
   __device__ __forceinline__ uint32_t* ctl() const { return base + gm_off::CTL; }
   __device__ __forceinline__ uint32_t* hist1(uint32_t par) const { return base + gm_off::HIST1 + par * HIST_BINS; }
-  __device__ __forceinline__ uint32_t* fine(uint32_t par) const { return base + gm_off::FINE + par * FINE_SLOTS * 16; }
-  __device__ __forceinline__ uint32_t* cov(uint32_t par) const { return base + gm_off::COV + par * FINE_SLOTS; }
+  __device__ __forceinline__ uint32_t* fine(uint32_t par) const { return base + gm_off::FINE + par * FINE_SLOTS * FINE_N; }
   __device__ __forceinline__ uint32_t* hist2(uint32_t q) const { return base + gm_off::HIST2 + q * DIG_BINS; }
   __device__ __forceinline__ uint32_t* rec() const { return base + gm_off::REC; }
-  __device__ __forceinline__ uint32_t* slots() const { return base + gm_off::REC + P * REC_W; }
+  __device__ __forceinline__ uint32_t* cnt() const { return base + gm_off::REC + P * REC_W; }
 };
 
 __device__ __forceinline__ GrpMem grp_mem(uint32_t* ws, uint32_t group, uint32_t P) {
@@ -153,21 +168,23 @@ struct GrpSelShared {
 
 struct GrpSmall {
   uint32_t scratch[8 * (GRP_NT / WAVE)];
-  uint32_t found[2];
+  uint32_t found[4];
   uint32_t red[DIG_BINS];            // one digit's counts, copies summed
-  uint32_t fwin[3 * 16 + WAVE];      // this workgroup's fine counts of its window
-  uint32_t fmrg[3 * 16 + 3];         // the group's merged fine counts and coverage of that window
-  uint32_t hist7[LAST_BINS + WAVE];  // last 7 bits of T (plus per-lane dummies)
+  uint32_t fwin[3 * FINE_N + WAVE];  // this workgroup's fine counts of its window
+  uint32_t fmrg[GRP_NT];             // the group's merged fine counts of that window, largest and smallest window
+  uint32_t h7a[LAST_BINS + WAVE], h7b[LAST_BINS + WAVE];  // last two 7-bit digits of T (plus per-lane dummies)
+  uint32_t hk[RLE_SLOTS], hc[RLE_SLOTS];   // distinct keys on the prefix (low bits + 1) and multiplicities
+  uint32_t rec[REC_W];               // this workgroup's record
   uint32_t misc[16];
-  // this workgroup's keys on the 16-bit prefix, in index order (exchange B):
-  // key, chunk offset, staged payload position
+  // this workgroup's keys on the 17-bit prefix, in index order (exchange B,
+  // at most WAVE of them): key, chunk offset, staged payload position
   uint32_t ckey[WAVE], coff[WAVE], cpos[WAVE];
   uint32_t rem[WAVE];                // staged positions dropped after exchange B, less their rank
 };
 
-// What exchange A leaves: the known leading bits of T, and the keys still to
-// place below them.  fine: the 16-bit prefix is known (every workgroup's guess
-// covered the bin of the k-th key).
+// The known leading bits of T, and the keys still to place below them.  fine:
+// exchange A found the 17-bit prefix (every workgroup's window covered the bin
+// of the k-th key).
 struct SelA {
   uint32_t prefix, pbits, need;
   bool fine;
@@ -177,7 +194,7 @@ struct SelA {
 struct GrpState {
   uint32_t nbar = 0;       // barriers passed (equal in all workgroups of the group)
   uint32_t iter = 0;       // segments handled
-  bool used_slots = false; // the fallback ran (its words must be cleared on exit)
+  bool used_cnt = false;   // the fallback ran (its counts must be cleared on exit)
 };
 
 // Histogram copies for digit counts: values that repeat (differences of
@@ -208,33 +225,32 @@ __device__ __forceinline__ void dig_reduce(const uint32_t* hist, uint32_t* red) 
   }
 }
 
-// After the second barrier of a segment every workgroup has read the
-// exchange A words of its parity: each clears a slice of them (histogram,
-// fine counts and coverage lie back to back).
+// After the barrier that follows exchange A's every workgroup has read the
+// exchange A words of its parity: each clears a slice of them.
 __device__ __forceinline__ void grp_clear_a(const GrpMem& g, uint32_t par, uint32_t P, uint32_t part) {
-  const uint32_t n1 = HIST_BINS, n2 = FINE_SLOTS * 16, n3 = FINE_SLOTS;
+  const uint32_t n1 = HIST_BINS, n2 = FINE_SLOTS * FINE_N;
   uint32_t* h1 = g.hist1(par);
   uint32_t* f1 = g.fine(par);
-  uint32_t* c1 = g.cov(par);
-  for (uint32_t i = part * GRP_NT + threadIdx.x; i < n1 + n2 + n3; i += P * GRP_NT) {
-    uint32_t* p = (i < n1) ? h1 + i : (i < n1 + n2) ? f1 + (i - n1) : c1 + (i - n1 - n2);
-    st_agent(p, 0u);
-  }
+  for (uint32_t i = part * GRP_NT + threadIdx.x; i < n1 + n2; i += P * GRP_NT) st_agent(i < n1 ? h1 + i : f1 + (i - n1), 0u);
+  if (part == 0 && threadIdx.x < 2) st_agent(&g.ctl()[32 + 2 * threadIdx.x + par], 0u);
 }
 
-// Exchange A for one segment held by the P workgroups of a group (this one
-// is `part`), k >= 1.  v[j][i] is element i of this thread's run j.
-// Elements past the segment's end hold +0: they have the smallest key and
-// the highest indices, so with k <= L they rank after every real element and
-// are never kept; the counts below need no bounds checks.  L: the segment's
-// length, rounded to what the group covers when the guess scales k.
-// Exchange A's first histogram (bits 30..19 of every key) and its window
-// counts, cleared before the workgroup's values arrive, so that the keys of
-// each run can be counted as soon as that run's loads land.
+// Exchange A's first histogram (bits 30..19 of every key) and the small
+// counters of both exchanges, cleared before the workgroup's values arrive,
+// so that the keys of each run can be counted as soon as that run's loads
+// land.
 template <int NT, typename SH>
 __device__ __forceinline__ void grp_hist_clear(SH& sh, GrpSmall& sm) {
   zero_lds<NT>(sh.hist, HIST_BINS);
-  if (threadIdx.x < 3 * 16) sm.fwin[threadIdx.x] = 0u;
+  const uint32_t t = threadIdx.x;
+  static_assert(NT >= 2 * LAST_BINS + 2 * (int)RLE_SLOTS + (int)REC_W && NT >= 3 * (int)FINE_N, "one word per thread");
+  if (t < 3 * FINE_N) sm.fwin[t] = 0u;
+  if (t < (uint32_t)LAST_BINS) sm.h7a[t] = 0u;
+  else if (t < 2u * LAST_BINS) sm.h7b[t - LAST_BINS] = 0u;
+  else if (t < 2u * LAST_BINS + RLE_SLOTS) sm.hk[t - 2u * LAST_BINS] = 0u;
+  else if (t < 2u * LAST_BINS + 2u * RLE_SLOTS) sm.hc[t - 2u * LAST_BINS - RLE_SLOTS] = 0u;
+  else if (t < 2u * LAST_BINS + 2u * RLE_SLOTS + REC_W) sm.rec[t - 2u * LAST_BINS - 2u * RLE_SLOTS] = 0u;
+  if (t == 0) sm.misc[4] = 0u;
   __syncthreads();
 }
 // One key into it; exact zeros (common after a ReLU, and the padding) are
@@ -247,206 +263,305 @@ __device__ __forceinline__ void grp_hist_add(SH& sh, uint32_t kk, uint32_t& zc) 
   atomicAdd(&sh.hist[pick(z, HIST_BINS + (uint32_t)lane_id(), kk >> 19)], 1u);
 }
 
-// Exchange A proper: every key of the workgroup is in the first histogram
-// (grp_hist_clear, then grp_hist_add per key; zc: this thread's exact zeros).
+// The bin of the merged first histogram that holds the k-th largest key:
+// found[0] (left alone when the counts do not reach k) and the keys in larger
+// bins found[1].  A thread that passes an address `word` loads it in the same
+// round trip into *to.
+template <int NT>
+__device__ __forceinline__ void grp_find_merged(const uint32_t* gh, uint32_t k, const uint32_t* word, uint32_t* to,
+                                                uint32_t* scratch, uint32_t* found) {
+  constexpr int BPT = HIST_BINS / NT;
+  static_assert(BPT >= 2 && BPT % 2 == 0, "two bins per 8-byte load");
+  uint32_t loc[BPT];
+  const uint64_t* p = reinterpret_cast<const uint64_t*>(gh + threadIdx.x * BPT);
+#pragma unroll
+  for (int i = 0; i < BPT / 2; ++i) {
+    const uint64_t w = ld_agent64(p + i);
+    loc[2 * i] = (uint32_t)w;
+    loc[2 * i + 1] = (uint32_t)(w >> 32);
+  }
+  if (word) *to = ld_agent(word);
+  find_bin_loc<NT, BPT>(loc, k, scratch, found);
+}
+
+// Exchange A for one segment held by the P > 1 workgroups of a group (this
+// one is `part`, with n_loc >= 1 elements of the segment), k >= 1; every key
+// of the workgroup is in the first histogram (grp_hist_clear, then
+// grp_hist_add per key; zc: this thread's exact zeros).  v[j][i] is element i
+// of this thread's run j.  Elements past the segment's end hold +0: they
+// have the smallest key and the highest indices, so with k <= L they rank
+// after every real element and are never kept; the counts need no bounds
+// checks.  The guess scales k by the elements the chunk really holds: a last
+// chunk that is only partly filled guesses as well as the others (scaled by
+// the whole chunk it missed, and every segment whose length is not a multiple
+// of the chunk took the digit passes: 5 x 100,003 binary16, TopK 30 %, sender
+// 25.4 us).
 template <int NT, int R, int E, uint32_t CH>
-__device__ __forceinline__ SelA grp_exchange_a(float (&v)[R][E], uint32_t zc, uint32_t k, uint64_t L, uint32_t P,
-                                               uint32_t part, const GrpMem& g,
+__device__ __forceinline__ SelA grp_exchange_a(float (&v)[R][E], uint32_t zc, uint32_t k, uint32_t n_loc, uint64_t L,
+                                               uint32_t P, uint32_t part, const GrpMem& g,
                                                GrpSelShared<grp_local_cap(CH)>& sh, GrpSmall& sm, GrpState& gs) {
-  const int t = (int)threadIdx.x;
+  const uint32_t t = threadIdx.x;
   auto key = [&](int j, int i) { return mag_key(v[j][i]); };
   const uint32_t par = gs.iter & 1u;
+  SelA A;
 
-  // ---- A: the exact zeros into the first histogram, once per wave
+  // ---- the exact zeros into the first histogram, once per wave
   const uint32_t zs = wave_sum(zc);
   if (lane_id() == 0 && zs) atomicAdd(&sh.hist[0], zs);
   __syncthreads();
 
-  uint32_t prefix, pbits, need;          // known leading bits of T, keys still to place
-  bool fine = false;
-  uint32_t lo = 0, hi = 0;
-  if (P > 1) {
-    // this workgroup's guess: its own bin at the same rank fraction
-    const uint32_t need_loc = (uint32_t)min<uint64_t>(max<uint64_t>(((uint64_t)k * CH + L - 1) / L, 1), CH);
-    find_bin<NT, HIST_BINS>(sh.hist, need_loc, sm.scratch, sm.found);
-    const uint32_t bh = sm.found[0];
-    lo = bh > 0u ? bh - 1u : 0u;
-    hi = min(bh + 1u, (uint32_t)HIST_BINS - 1u);
-    // bits 18..15 of the keys in bins lo..hi (the exact zeros, whose bits
-    // 18..15 are 0, once per wave)
-    refresh(v);
+  // this workgroup's guess: its own bin at the same rank fraction
+  const uint32_t need_loc = (uint32_t)min<uint64_t>(max<uint64_t>(((uint64_t)k * n_loc + L - 1) / L, 1), n_loc);
+  find_bin<NT, HIST_BINS>(sh.hist, need_loc, sm.scratch, sm.found);
+  const uint32_t bh = sm.found[0];
+  const uint32_t lo = bh > 0u ? bh - 1u : 0u;
+  const uint32_t hi = min(bh + 1u, (uint32_t)HIST_BINS - 1u);
+  // bits 18..14 of the keys in bins lo..hi (the exact zeros, whose bits
+  // 18..14 are 0, once per wave)
+  refresh(v);
 #pragma unroll
-    for (int j = 0; j < R; ++j)
+  for (int j = 0; j < R; ++j)
 #pragma unroll
-      for (int i = 0; i < E; ++i) {
-        const uint32_t kk = key(j, i), b = kk >> 19;
-        // in the window lo..hi (b - lo < 3, unsigned) and not an exact zero
-        const uint32_t in = gt31(3u, b - lo) & (eq31(kk, 0u) ^ 1u) & (gt31(lo, b) ^ 1u);
-        atomicAdd(&sm.fwin[pick(in, (b - lo) * 16u + ((kk >> 15) & 15u), 3u * 16u + (uint32_t)lane_id())], 1u);
-      }
-    if (lo == 0u && lane_id() == 0 && zs) atomicAdd(&sm.fwin[0], zs);
-    __syncthreads();
-    // merge into the group's counts
-    uint32_t* h1 = g.hist1(par);
-    uint32_t* f1 = g.fine(par);
-    uint32_t* c1 = g.cov(par);
-    for (int b = t; b < HIST_BINS; b += NT)
-      if (sh.hist[b]) add_agent(&h1[b], sh.hist[b]);
-    if (t < 3 * 16) {
-      const uint32_t b = lo + (uint32_t)t / 16u;
-      if (b <= hi && sm.fwin[t]) add_agent(&f1[(b & (FINE_SLOTS - 1)) * 16u + (uint32_t)t % 16u], sm.fwin[t]);
-    } else if (t < 3 * 16 + 3) {
-      const uint32_t b = lo + (uint32_t)(t - 3 * 16);
-      if (b <= hi) add_agent(&c1[b & (FINE_SLOTS - 1)], 1u + ((b >> 8) << 16));
+    for (int i = 0; i < E; ++i) {
+      const uint32_t kk = key(j, i), b = kk >> 19;
+      // in the window lo..hi (b - lo < 3, unsigned) and not an exact zero
+      const uint32_t in = gt31(3u, b - lo) & (eq31(kk, 0u) ^ 1u) & (gt31(lo, b) ^ 1u);
+      atomicAdd(&sm.fwin[pick(in, (b - lo) * FINE_N + ((kk >> LOW_BITS) & (FINE_N - 1u)), 3u * FINE_N + (uint32_t)lane_id())], 1u);
     }
-    group_sync(g.ctl(), P * ++gs.nbar);
-    // everybody has read the previous segment's exchange B counts: clear a slice
-    if (gs.iter > 0)
-      for (int b = (int)(part * NT) + t; b < (int)DIG_BINS; b += (int)(P * NT)) st_agent(&g.hist2(par ^ 1u)[b], 0u);
-    // one round trip: the merged histogram, the fine counts and coverage of this window
-    uint32_t fw = 0;
-    if (t < 3 * 16 + 3) {
-      const uint32_t b = lo + (uint32_t)(t < 48 ? t / 16 : t - 48);
-      if (b <= hi) fw = ld_agent(t < 48 ? &f1[(b & (FINE_SLOTS - 1)) * 16u + (uint32_t)t % 16u] : &c1[b & (FINE_SLOTS - 1)]);
-    }
-    find_bin_global<NT>(h1, k, sm.scratch, sm.found);
-    const uint32_t b1 = sm.found[0];
-    need = k - sm.found[1];
-    if (t < 3 * 16 + 3) sm.fmrg[t] = fw;
-    __syncthreads();
-    fine = b1 >= lo && b1 <= hi && sm.fmrg[48 + (b1 - lo)] == P + ((P * (b1 >> 8)) << 16);
-    prefix = b1;
-    pbits = 12;
-    if (fine) {
-      // bits 18..15 of T from the merged fine counts of b1 (every thread alike)
-      const uint32_t* f = &sm.fmrg[(b1 - lo) * 16u];
-      uint32_t acc = 0, f1v = 16;
-      for (int q = 15; q >= 0; --q) {
-        const uint32_t c = f[q];
-        if (acc < need && need <= acc + c) { f1v = (uint32_t)q; break; }
-        acc += c;
-      }
-      if (f1v < 16) {
-        prefix = (b1 << 4) | f1v;
-        pbits = 16;
-        need -= acc;
-      } else {
-        fine = false;   // inconsistent counts: never expected; take the exact passes
-      }
-    }
-    __syncthreads();
-  } else {
-    find_bin<NT, HIST_BINS>(sh.hist, k, sm.scratch, sm.found);
-    prefix = sm.found[0];
-    pbits = 12;
-    need = k - sm.found[1];
-    __syncthreads();
+  if (lo == 0u && lane_id() == 0 && zs) atomicAdd(&sm.fwin[0], zs);
+  __syncthreads();
+  // merge into the group's counts
+  uint32_t* h1 = g.hist1(par);
+  uint32_t* gmax = g.ctl() + 32 + par;
+  uint32_t* gmin = g.ctl() + 34 + par;
+  const uint32_t first = sat_sub(lo, A_MARGIN);
+  for (uint32_t b = (first & ~(uint32_t)(NT - 1)) + t; b < (uint32_t)HIST_BINS; b += NT)
+    if (b >= first && sh.hist[b]) add_agent(&h1[b], sh.hist[b]);
+  const uint32_t* word = nullptr;   // the word this thread reads back with the histogram
+  if (t < 3 * FINE_N) {
+    const uint32_t b = lo + t / FINE_N;
+    uint32_t* f = &g.fine(par)[(b & (FINE_SLOTS - 1)) * FINE_N + t % FINE_N];
+    if (b <= hi && sm.fwin[t]) add_agent(f, sm.fwin[t]);
+    word = f;
+  } else if (t == 3 * FINE_N) {
+    __hip_atomic_fetch_max(gmax, lo + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    word = gmax;
+  } else if (t == 3 * FINE_N + 1) {
+    __hip_atomic_fetch_max(gmin, (uint32_t)HIST_BINS - lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    word = gmin;
   }
-  SelA A;
-  A.prefix = prefix;
-  A.pbits = pbits;
-  A.need = need;
-  A.fine = fine;
+  if (t == 0) sm.found[0] = ~0u;
+  group_sync(g.ctl(), P * ++gs.nbar);
+  // one round trip: the merged histogram, this window's fine counts, the
+  // smallest and largest window
+  grp_find_merged<NT>(h1, k, word, &sm.fmrg[t], sm.scratch, sm.found);
+  uint32_t b1 = sm.found[0];
+  const uint32_t lo_max = sm.fmrg[3 * FINE_N] - 1u, lo_min = (uint32_t)HIST_BINS - sm.fmrg[3 * FINE_N + 1];
+  // every window covers b1 (this one's too): bits 18..14 of T from the
+  // merged fine counts of b1, by every wavefront alike
+  A.fine = b1 != ~0u && lo_max <= b1 && b1 <= lo_min + 2u && b1 - lo <= 2u;
+  if (A.fine) {
+    const uint32_t need = k - sm.found[1], lane = (uint32_t)lane_id();
+    const uint32_t c = (lane < FINE_N) ? sm.fmrg[(b1 - lo) * FINE_N + (FINE_N - 1u - lane)] : 0u;
+    const uint32_t incl = wave_incl_scan(c);
+    const uint64_t hit = __ballot(lane < FINE_N && incl >= need);
+    const int l = hit ? __builtin_ctzll(hit) : 0;   // (a hit is certain: the counts are complete)
+    A.prefix = (b1 << FINE_BITS) | (FINE_N - 1u - (uint32_t)l);
+    A.pbits = 12 + FINE_BITS;
+    A.need = need - (uint32_t)__builtin_amdgcn_readlane((int)(incl - c), l);
+    __syncthreads();
+    return A;
+  }
+  if (b1 == ~0u || b1 < sat_sub(lo_max, A_MARGIN)) {
+    // some workgroup left out bins at or above b1: the rest of the counts,
+    // then the search again
+    __syncthreads();   // (everybody has read found[])
+    for (uint32_t b = t; b < first; b += NT)
+      if (sh.hist[b]) add_agent(&h1[b], sh.hist[b]);
+    if (t == 0) sm.found[0] = 0u;
+    group_sync(g.ctl(), P * ++gs.nbar);
+    grp_find_merged<NT>(h1, k, nullptr, nullptr, sm.scratch, sm.found);
+    b1 = sm.found[0];
+  }
+  A.prefix = b1;
+  A.pbits = 12;
+  A.need = k - sm.found[1];
+  __syncthreads();
   return A;
 }
 
-// Exchange B (fine mode), first half.  Before calling, this workgroup has
-// written the keys that share the 16-bit prefix into its record (slots 2..,
-// at most REC_KEYS of them), counted their bits 14..7 into sm.red (followed
-// by a barrier), and knows how many of its keys lie above the prefix
-// (abv_wg) and on it (cnt_wg).  Publishes the counts and arrives at the
-// group's barrier; the workgroup may work on its own until grp_finish_b.
-template <int NT>
-__device__ __forceinline__ void grp_publish_b(uint32_t part, const GrpMem& g, const GrpSmall& sm, GrpState& gs,
-                                              uint32_t abv_wg, uint32_t cnt_wg) {
+// One digit pass (pass p of the segment): the next w <= 8 bits of the keys
+// that share the known prefix, counted by every workgroup and merged through
+// hist2(p).
+template <int NT, int R, int E, typename SH>
+__device__ __forceinline__ void grp_pass(float (&v)[R][E], uint32_t w, uint32_t p, uint32_t P, const GrpMem& g, SH& sh,
+                                         GrpSmall& sm, GrpState& gs, SelA& A) {
   const int t = (int)threadIdx.x;
-  uint32_t* my = g.rec() + (uint64_t)part * REC_W;
-  uint32_t* h2 = g.hist2(gs.iter & 1u);
+  const uint32_t left = 31u - A.pbits, shift = left - w;
+  dig_zero<NT>(sh.hist);
+  __syncthreads();
+  refresh(v);
+#pragma unroll
+  for (int j = 0; j < R; ++j)
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      const uint32_t kk = mag_key(v[j][i]);
+      dig_add(sh.hist, (kk >> left) == A.prefix, (kk >> shift) & ((1u << w) - 1u));
+    }
+  __syncthreads();
+  dig_reduce<NT, 256>(sh.hist, sm.red);
+  __syncthreads();
+  uint32_t* h2 = g.hist2(p);
   if (t < (int)DIG_BINS && sm.red[t]) add_agent(&h2[t], sm.red[t]);
-  if (t == 0) { st_agent(&my[0], abv_wg); st_agent(&my[1], cnt_wg); }
-  ++gs.nbar;
-  group_arrive(g.ctl());
+  group_sync(g.ctl(), P * ++gs.nbar);
+  if (t < (int)DIG_BINS) sm.red[t] = ld_agent(&h2[t]);
+  __syncthreads();
+  find_bin_wave<256>(sm.red, A.need, sm.found);
+  A.prefix = (A.prefix << w) | sm.found[0];
+  A.pbits += w;
+  A.need -= sm.found[1];
+  __syncthreads();
+}
+// after a later barrier everybody has read pass p's counts: each workgroup
+// clears a slice of them
+__device__ __forceinline__ void grp_clear_pass(const GrpMem& g, uint32_t p, uint32_t P, uint32_t part) {
+  uint32_t* h2 = g.hist2(p);
+  for (uint32_t b = part * GRP_NT + threadIdx.x; b < DIG_BINS; b += P * GRP_NT) st_agent(&h2[b], 0u);
 }
 
-// Exchange B, second half: waits for the group, reads all records and the
-// merged digit counts in one round trip and finds T, the tie quota and the
-// larger keys and ties of lower workgroups (the last after one more barrier,
-// by grp_finish_b_lower).  Returns false (nothing decided)
-// when some record could not hold its keys; exchange A's words are cleared
-// either way.
+// One of this workgroup's keys on the prefix (its low bits), c times, into
+// the table of distinct keys.  A table too full to place it raises misc[4]:
+// the record is then marked as overflowed.
+__device__ __forceinline__ void grp_rle_add(GrpSmall& sm, uint32_t low, uint32_t c) {
+  uint32_t h = ((low * 0x9E5u) >> 4) & (RLE_SLOTS - 1u);
+  for (uint32_t p = 0; p < RLE_PROBES; ++p) {
+    const uint32_t old = atomicCAS(&sm.hk[h], 0u, low + 1u);
+    if (old == 0u || old == low + 1u) {
+      atomicAdd(&sm.hc[h], c);
+      return;
+    }
+    h = (h + 1u) & (RLE_SLOTS - 1u);
+  }
+  sm.misc[4] = 1u;
+}
+
+// Exchange B (fine mode), first half.  A record is a header (the keys above
+// the prefix, below 2^16, and REC_OVF << 16 when its keys did not fit) and
+// entries: a key's low bits and its multiplicity << LOW_BITS (at most 12,288;
+// an unused entry is 0).  Before calling, this workgroup has either put one
+// entry per key on the prefix into sm.rec (direct) or its keys into the table
+// of distinct keys.  The first wavefront stores the record with one
+// instruction and arrives at the group's barrier; nobody waits here.
 template <int NT>
-__device__ __forceinline__ bool grp_finish_b(uint32_t k, uint32_t P, uint32_t part, const GrpMem& g, GrpSmall& sm,
-                                             GrpState& gs, const SelA& A, SelResult& res) {
+__device__ __forceinline__ void grp_publish_b(uint32_t part, const GrpMem& g, GrpSmall& sm, GrpState& gs,
+                                              uint32_t abv_wg, bool direct) {
+  __syncthreads();   // the entries or the table are complete
+  ++gs.nbar;
+  if (threadIdx.x >= WAVE) return;
+  const uint32_t lane = threadIdx.x;
+  uint32_t hdr = abv_wg;
+  if (!direct) {
+    const uint32_t kx = sm.hk[lane], c = sm.hc[lane];
+    const uint64_t in = __ballot(kx != 0u);
+    const uint32_t q = lanes_below(in);
+    if (kx != 0u && q < REC_KEYS) sm.rec[1 + q] = (kx - 1u) | (c << LOW_BITS);
+    if ((uint32_t)__popcll(in) > REC_KEYS || sm.misc[4] != 0u) hdr |= REC_OVF << 16;
+  }
+  // (a wavefront's LDS accesses complete in program order)
+  __builtin_amdgcn_wave_barrier();
+  if (lane < REC_W) st_agent(&g.rec()[(uint64_t)part * REC_W + lane], lane == 0 ? hdr : sm.rec[lane]);
+  __builtin_amdgcn_s_waitcnt(0);
+  if (lane == 0) __hip_atomic_fetch_add(g.ctl(), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// the bin d of a 128-bin histogram in LDS with  sum_{c > d} h[c] < need <=
+// sum_{c >= d} h[c], and that first sum; every wavefront finds it alike
+__device__ __forceinline__ void wave_find128(const uint32_t* h, uint32_t need, uint32_t& d, uint32_t& above) {
+  const uint32_t lane = (uint32_t)lane_id();
+  const uint32_t c0 = h[2 * lane], c1 = h[2 * lane + 1], sum = c0 + c1;
+  const uint32_t incl = wave_incl_scan(sum);
+  const uint32_t acc = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1) - incl;   // bins of higher lanes
+  const uint64_t hit = __ballot(acc < need && need <= acc + sum);
+  const uint32_t dd = (acc + c1 >= need) ? 2 * lane + 1 : 2 * lane;
+  const uint32_t aa = (acc + c1 >= need) ? acc : acc + c1;
+  const int l = hit ? __builtin_ctzll(hit) : 0;   // (a hit is certain: the counts cover need)
+  d = (uint32_t)__builtin_amdgcn_readlane((int)dd, l);
+  above = (uint32_t)__builtin_amdgcn_readlane((int)aa, l);
+}
+
+// Exchange B, second half: waits for the group, reads all records in one
+// round trip (SPT words per thread: up to 16 * SPT workgroups) and finds T,
+// the tie quota and the larger keys and ties of lower workgroups (the last
+// after one more barrier, by grp_finish_b_lower).  Returns false (nothing
+// decided) when some record could not hold its keys; the words of exchange A
+// (fine) or of the digit pass after it are cleared either way.
+template <int NT, int SPT>
+__device__ __forceinline__ bool grp_finish_b(uint32_t P, uint32_t part, const GrpMem& g, GrpSmall& sm, GrpState& gs,
+                                             const SelA& A, SelResult& res) {
   constexpr int NW = NT / WAVE;
-  constexpr int SPT = (int)(REC_P_MAX * REC_W / NT);
-  static_assert(NT % REC_W == 0 && REC_W == WAVE, "a record is one word per lane of a wavefront");
-  const int t = (int)threadIdx.x, wv = t / WAVE, lane = lane_id();
-  const uint32_t par = gs.iter & 1u;
+  static_assert(REC_W * 2 == WAVE, "two records per wavefront read");
+  const uint32_t t = threadIdx.x, wv = t / WAVE, lane = (uint32_t)lane_id();
+  const uint32_t half = lane / REC_W, wi = lane % REC_W;
   group_wait(g.ctl(), P * gs.nbar);
-  grp_clear_a(g, par, P, part);
-  // lane i of wavefront wv reads word i of records u*NW + wv
-  uint32_t hd = 0;
-  if (t < (int)DIG_BINS) hd = ld_agent(&g.hist2(par)[t]);
+  // lane i of wavefront wv reads word i % 32 of record 2 * (u*NW + wv) + i / 32
   const uint32_t* rec = g.rec();
   uint32_t wd[SPT];
 #pragma unroll
   for (int u = 0; u < SPT; ++u) {
-    const uint32_t w = (uint32_t)(u * NW + wv);
-    wd[u] = (w < P) ? ld_agent(&rec[(uint64_t)w * REC_W + (uint32_t)lane]) : 0u;
+    const uint32_t w = 2u * (uint32_t)(u * NW + wv) + half;
+    wd[u] = (w < P) ? ld_agent(&rec[(uint64_t)w * REC_W + wi]) : 0u;
   }
-  // totals from the record headers (words 0 and 1 sit in lanes 0 and 1)
-  uint32_t cnt[SPT], abv_bef = 0, abv_all = 0, bad = 0;
+  if (A.fine) grp_clear_a(g, gs.iter & 1u, P, part);
+  else grp_clear_pass(g, 0, P, part);
+  // headers (lanes 0 and 32) give the keys above the prefix before this
+  // workgroup; entries count into the histogram of their bits 13..7
+  uint32_t abv = 0, bad = 0;
 #pragma unroll
   for (int u = 0; u < SPT; ++u) {
-    const uint32_t w = (uint32_t)(u * NW + wv);
-    const uint32_t aw = __builtin_amdgcn_readlane(wd[u], 0);
-    cnt[u] = __builtin_amdgcn_readlane(wd[u], 1);
-    abv_all += aw;
-    abv_bef += (w < part) ? aw : 0u;
-    bad |= (cnt[u] > REC_KEYS) ? 1u : 0u;
+    const uint32_t w = 2u * (uint32_t)(u * NW + wv) + half;
+    abv += (wi == 0u && w < part) ? wd[u] & 0xFFFFu : 0u;
+    bad |= (wi == 0u) ? wd[u] >> 16 : 0u;
+    wd[u] = (wi == 0u) ? 0u : wd[u];
+    const uint32_t c = wd[u] >> LOW_BITS;
+    atomicAdd(&sm.h7a[c ? (wd[u] >> 7) & 0x7Fu : (uint32_t)LAST_BINS + lane], c);
   }
-  uint32_t* tsc = sm.scratch + 5 * NW;   // clear of the scans' words
-  if (lane == 0) { tsc[wv] = abv_bef; tsc[NW + wv] = abv_all; tsc[2 * NW + wv] = bad; }
-  if (t < (int)DIG_BINS) sm.red[t] = hd;
-  if (t < (int)LAST_BINS) sm.hist7[t] = 0u;
+  abv = wave_sum(abv);
+  const bool wbad = __ballot(bad != 0u) != 0u;
+  uint32_t* tsc = sm.scratch + 5 * NW;   // clear of the sums below
+  if (lane == 0) { tsc[wv] = abv; tsc[NW + wv] = wbad ? 1u : 0u; }
   __syncthreads();
-  abv_bef = 0;
-  abv_all = 0;
+  uint32_t abv_bef = 0;
   bad = 0;
 #pragma unroll
-  for (int i = 0; i < NW; ++i) { abv_bef += tsc[i]; abv_all += tsc[NW + i]; bad |= tsc[2 * NW + i]; }
+  for (int i = 0; i < NW; ++i) { abv_bef += tsc[i]; bad |= tsc[NW + i]; }
   if (bad != 0) return false;
-  // bits 14..7 of T from the merged digit counts; bits 6..0 from the inline
-  // keys that share the 24-bit prefix
-  uint32_t c[SPT];
-  bool lower[SPT];
+  uint32_t da, db, above;
+  wave_find128(sm.h7a, A.need, da, above);
+  const uint32_t need_c = A.need - above;
 #pragma unroll
   for (int u = 0; u < SPT; ++u) {
-    const uint32_t w = (uint32_t)(u * NW + wv);
-    const bool valid = lane >= 2 && (uint32_t)(lane - 2) < cnt[u];   // cnt is 0 past the last record
-    c[u] = valid ? wd[u] : ~0u;           // ~0u matches no prefix
-    lower[u] = valid && w < part;
+    const uint32_t c = (((wd[u] >> 7) & 0x7Fu) == da) ? wd[u] >> LOW_BITS : 0u;
+    atomicAdd(&sm.h7b[c ? wd[u] & 0x7Fu : (uint32_t)LAST_BINS + lane], c);
   }
-  const uint32_t need_b = k - abv_all;
-  find_bin_wave<256>(sm.red, need_b, sm.found);
-  const uint32_t p24 = (A.prefix << 8) | sm.found[0];
-  const uint32_t need_c = need_b - sm.found[1];
-  const uint32_t dummy = LAST_BINS + (uint32_t)lane;
-#pragma unroll
-  for (int u = 0; u < SPT; ++u) atomicAdd(&sm.hist7[(c[u] >> 7) == p24 ? (c[u] & 0x7Fu) : dummy], 1u);
   __syncthreads();
-  find_bin_wave<LAST_BINS>(sm.hist7, need_c, sm.found);
-  res.T = (p24 << 7) | sm.found[0];
-  res.r = need_c - sm.found[1];
-  // larger keys and ties in lower workgroups' records (both below 2^16),
-  // summed per wavefront into sm.scratch[0..NW): grp_finish_b_lower adds
-  // them up after the caller's next barrier
-  uint32_t ge = 0;
+  wave_find128(sm.h7b, need_c, db, above);
+  const uint32_t low = (da << 7) | db;
+  res.T = (A.prefix << (31u - A.pbits)) | low;
+  res.r = need_c - above;
+  // larger keys and ties in lower workgroups' records, summed per wavefront
+  // into sm.scratch: grp_finish_b_lower adds them up after the caller's next
+  // barrier
+  uint32_t gt = 0, eq = 0;
 #pragma unroll
-  for (int u = 0; u < SPT; ++u)
-    ge += (lower[u] && c[u] > res.T) ? 1u : ((lower[u] && c[u] == res.T) ? 0x10000u : 0u);
-  ge = wave_sum(ge);
-  if (lane == 0) sm.scratch[wv] = ge;
+  for (int u = 0; u < SPT; ++u) {
+    const uint32_t w = 2u * (uint32_t)(u * NW + wv) + half;
+    const uint32_t c = (w < part) ? wd[u] >> LOW_BITS : 0u, kl = wd[u] & ((1u << LOW_BITS) - 1u);
+    gt += (kl > low) ? c : 0u;
+    eq += (kl == low) ? c : 0u;
+  }
+  gt = wave_sum(gt);
+  eq = wave_sum(eq);
+  if (lane == 0) { sm.scratch[wv] = gt; sm.scratch[NW + wv] = eq; }
   res.gt_before = abv_bef;
   res.eq_before = 0;
   return true;
@@ -454,127 +569,54 @@ __device__ __forceinline__ bool grp_finish_b(uint32_t k, uint32_t P, uint32_t pa
 
 template <int NT>
 __device__ __forceinline__ void grp_finish_b_lower(const GrpSmall& sm, SelResult& res) {
-  uint32_t sge = 0;
+  constexpr int NW = NT / WAVE;
 #pragma unroll
-  for (int i = 0; i < NT / WAVE; ++i) sge += sm.scratch[i];
-  res.gt_before += sge & 0xFFFFu;
-  res.eq_before = sge >> 16;
+  for (int i = 0; i < NW; ++i) { res.gt_before += sm.scratch[i]; res.eq_before += sm.scratch[NW + i]; }
 }
 
-// The exact passes from the prefix exchange A (or B) left: 8-bit digit
-// passes merged through device memory, then a last digit of at most 8 bits
-// counted per workgroup (slots), which also gives what precedes this
-// workgroup.  `cleared`: exchange A's words have already been cleared.
+// The exact passes once a record overflowed: digit passes of up to 8 bits
+// merged through device memory until T is known, then one exchange of every
+// workgroup's counts of larger keys and ties, which gives what precedes this
+// workgroup.  `pass`: digit passes already done for this segment.
 template <int NT, int R, int E, uint32_t CH>
 __device__ __forceinline__ SelResult grp_fallback(float (&v)[R][E], uint32_t P, uint32_t part, const GrpMem& g,
                                                   GrpSelShared<grp_local_cap(CH)>& sh, GrpSmall& sm, GrpState& gs,
-                                                  uint32_t prefix, uint32_t pbits, uint32_t need, bool cleared) {
+                                                  SelA A, uint32_t pass) {
   const int t = (int)threadIdx.x;
   auto key = [&](int j, int i) { return mag_key(v[j][i]); };
-  const uint32_t par = gs.iter & 1u;
-  SelResult res;
-  gs.used_slots = gs.used_slots || P > 1;
-  for (int pass = 0; 31u - pbits > 8u; ++pass) {
-    const uint32_t sh8 = 31u - pbits - 8u;         // the digit's lowest bit
-    dig_zero<NT>(sh.hist);
-    __syncthreads();
-    refresh(v);
-#pragma unroll
-    for (int j = 0; j < R; ++j)
-#pragma unroll
-      for (int i = 0; i < E; ++i) {
-        const uint32_t kk = key(j, i);
-        dig_add(sh.hist, (kk >> (sh8 + 8u)) == prefix, (kk >> sh8) & 0xFFu);
-      }
-    __syncthreads();
-    dig_reduce<NT, 256>(sh.hist, sm.red);
-    __syncthreads();
-    if (P > 1) {
-      // at most two passes per segment, each with its own counts (cleared
-      // after the last-digit barrier)
-      uint32_t* h2 = g.hist2(2u + (uint32_t)pass);
-      if (t < (int)DIG_BINS && sm.red[t]) add_agent(&h2[t], sm.red[t]);
-      group_sync(g.ctl(), P * ++gs.nbar);
-      if (t < (int)DIG_BINS) sm.red[t] = ld_agent(&h2[t]);
-      if (!cleared) { grp_clear_a(g, par, P, part); cleared = true; }
-      __syncthreads();
-    }
-    find_bin_wave<256>(sm.red, need, sm.found);
-    prefix = (prefix << 8) | sm.found[0];
-    pbits += 8;
-    need -= sm.found[1];
-    __syncthreads();
+  const uint32_t first = pass;
+  // at most three passes per segment, each with its own counts
+  for (; A.pbits < 31u; ++pass) {
+    grp_pass<NT, R, E>(v, min(8u, 31u - A.pbits), pass, P, g, sh, sm, gs, A);
+    if (pass > first) grp_clear_pass(g, pass - 1, P, part);
   }
-  // last digit: per-workgroup counts, published as transposed slots
-  const uint32_t lb = 31u - pbits;                  // 1..8 bits
-  const uint32_t nbl = 1u << lb;
-  dig_zero<NT>(sh.hist);
-  __syncthreads();
+  SelResult res;
+  res.T = A.prefix;
+  res.r = A.need;
+  // larger keys and ties of every workgroup (both below 2^16)
   refresh(v);
-  uint32_t gtp = 0;   // keys with a larger prefix
+  uint32_t ge = 0;
 #pragma unroll
   for (int j = 0; j < R; ++j)
 #pragma unroll
     for (int i = 0; i < E; ++i) {
       const uint32_t kk = key(j, i);
-      dig_add(sh.hist, (kk >> lb) == prefix, kk & (nbl - 1u));
-      gtp += ((kk >> lb) > prefix) ? 1u : 0u;
+      ge += gt31(kk, res.T) | (eq31(kk, res.T) << 16);
     }
-  const uint32_t gtp_wg = block_sum<NT>(gtp, sm.scratch);   // contains barriers
-  dig_reduce<NT, 256>(sh.hist, sm.red);
-  __syncthreads();
-  uint32_t* hall = sh.cand;                 // [256] whole segment
-  uint32_t* hbef = sh.cand + DIG_BINS;      // [256] lower workgroups
-  uint32_t gtpb = 0;
-  if (P > 1) {
-    const uint32_t pitch = slot_pitch(P);
-    uint32_t* slots = g.slots();
-    if (t < (int)DIG_BINS) st_agent(&slots[(uint64_t)t * pitch + part], sm.red[t]);
-    if (t == 0) st_agent(&slots[(uint64_t)DIG_BINS * pitch + part], gtp_wg);
-    group_sync(g.ctl(), P * ++gs.nbar);
-    if (!cleared) { grp_clear_a(g, par, P, part); cleared = true; }
-    // every digit pass has been read by everybody: clear a slice of their counts
-    for (int b = (int)(part * NT) + t; b < (int)(2 * DIG_BINS); b += (int)(P * NT)) st_agent(&g.hist2(2)[b], 0u);
-    // row `bin` of the slots holds that bin's count in every workgroup; two
-    // thread sets split each row and read it in 8-byte pairs
-    constexpr int SETS = NT / (int)DIG_BINS;
-    const int bin = t % (int)DIG_BINS, set = t / (int)DIG_BINS;
-    const uint32_t per = pitch / SETS;          // even: pitch is a multiple of 8
-    const uint64_t* row = reinterpret_cast<const uint64_t*>(slots + (uint64_t)bin * pitch + set * per);
-    uint32_t a_all = 0, a_bef = 0;
-    for (uint32_t q = 0; q < per / 2; ++q) {
-      const uint64_t pr = ld_agent64(row + q);
-      const uint32_t jw = set * per + 2 * q;
-      const uint32_t lo2 = (uint32_t)pr, hi2 = (uint32_t)(pr >> 32);
-      a_all += lo2 + hi2;
-      a_bef += (jw < part ? lo2 : 0u) + (jw + 1 < part ? hi2 : 0u);
-    }
-    uint32_t g_own = 0;
-    for (uint32_t q = (uint32_t)t; q < part; q += NT) g_own += ld_agent(slots + (uint64_t)DIG_BINS * pitch + q);
-    uint32_t* red = sh.hist;   // [SETS][2][256] partial sums (free now)
-    red[(set * 2) * DIG_BINS + bin] = a_all;
-    red[(set * 2 + 1) * DIG_BINS + bin] = a_bef;
-    __syncthreads();
-    if (t < (int)DIG_BINS) {
-      uint32_t s_all = 0, s_bef = 0;
-#pragma unroll
-      for (int q = 0; q < SETS; ++q) { s_all += red[(q * 2) * DIG_BINS + t]; s_bef += red[(q * 2 + 1) * DIG_BINS + t]; }
-      hall[t] = s_all;
-      hbef[t] = s_bef;
-    }
-    gtpb = block_sum<NT>(g_own, sm.scratch);
-  } else {
-    if (t < (int)DIG_BINS) { hall[t] = sm.red[t]; hbef[t] = 0u; }
+  const uint32_t ge_wg = block_sum<NT>(ge, sm.scratch);
+  uint32_t* cnt = g.cnt();
+  gs.used_cnt = true;
+  if (t == 0) st_agent(&cnt[part], ge_wg);
+  group_sync(g.ctl(), P * ++gs.nbar);
+  uint32_t gt = 0, eq = 0;
+  for (uint32_t q = (uint32_t)t; q < part; q += NT) {
+    const uint32_t c = ld_agent(&cnt[q]);
+    gt += c & 0xFFFFu;
+    eq += c >> 16;
   }
-  __syncthreads();
-  find_bin_wave<256>(hall, need, sm.found);
-  const uint32_t d = sm.found[0];
-  res.T = (prefix << lb) | d;
-  res.r = need - sm.found[1];
-  const uint32_t gt_digit = (t < (int)DIG_BINS && (uint32_t)t > d) ? hbef[t] : 0u;
-  res.gt_before = gtpb + block_sum<NT>(gt_digit, sm.scratch);
-  res.eq_before = hbef[d];
-  __syncthreads();
+  grp_clear_pass(g, pass - 1, P, part);
+  res.gt_before = block_sum<NT>(gt, sm.scratch);
+  res.eq_before = block_sum<NT>(eq, sm.scratch);
   return res;
 }
 
@@ -582,8 +624,8 @@ __device__ __forceinline__ SelResult grp_fallback(float (&v)[R][E], uint32_t P, 
 // once it has read the last exchange words (grp_exit_ticket: the atomic is
 // issued, nobody waits for it); at its very end, the workgroup that drew the
 // last ticket (all others have finished reading) clears the barrier words,
-// the records, exchange B's digit counts of both parities and, if the
-// fallback ran, the slots; everything else is cleared in flight.
+// the records and, if the fallback ran, the workgroups' counts; everything
+// else is cleared in flight.
 __device__ __forceinline__ uint32_t grp_exit_ticket(const GrpMem& g) {
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
@@ -598,15 +640,10 @@ __device__ __forceinline__ void grp_exit_finish(const GrpMem& g, uint32_t P, con
   if (threadIdx.x == 0) *flag = (ticket == P - 1) ? 1u : 0u;
   __syncthreads();
   if (!*flag) return;
-  const uint64_t nrec = (uint64_t)P * REC_W;
+  // the records and the counts lie back to back
+  const uint32_t n = P * REC_W + (gs.used_cnt ? P : 0u);
   uint32_t* rec = g.rec();
-  for (uint64_t i = threadIdx.x; i < nrec; i += NT) st_agent(&rec[i], 0u);
-  for (uint32_t i = threadIdx.x; i < 2 * DIG_BINS; i += NT) st_agent(&g.hist2(0)[i], 0u);
-  if (gs.used_slots) {
-    const uint64_t n = (uint64_t)DIG_ROWS * slot_pitch(P);
-    uint32_t* slots = g.slots();
-    for (uint64_t i = threadIdx.x; i < n; i += NT) st_agent(&slots[i], 0u);
-  }
+  for (uint32_t i = threadIdx.x; i < n; i += NT) st_agent(&rec[i], 0u);
   if (threadIdx.x == 0) {
     st_agent(g.ctl(), 0u);
     st_agent(g.ctl() + 1, 0u);

@@ -5,8 +5,7 @@
 // key T and the tie quota r = k - #(key > T) define the kept set:
 //   key > T, or key == T and the entry is among the r lowest-index ties.
 //
-// Shared pieces: bin search over histograms (in LDS or merged in device
-// memory), and the one-wavefront strategy for short segments (a token row):
+// Shared pieces: bin search over histograms in LDS, and the one-wavefront strategy for short segments (a token row):
 // a radix select over 8-bit digits with a wavefront-private histogram.  The
 // several-workgroup strategy is in tc_group.hpp.
 #pragma once
@@ -17,11 +16,6 @@ namespace tc {
 
 constexpr int HIST_BINS = 4096;   // 12-bit digits for the first two passes
 constexpr int LAST_BINS = 128;    // 7-bit digit for the last pass
-constexpr int SLOT_ROWS = LAST_BINS + 1;   // per-workgroup slot: 128 bins + larger-prefix count
-
-// slot rows are laid out transposed, [row][workgroup], each row padded to a
-// multiple of 8 workgroups so that readers can take them in 8-byte pairs
-__host__ __device__ constexpr uint32_t slot_pitch(uint32_t P) { return (P + 7u) & ~7u; }
 
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
@@ -67,24 +61,6 @@ __device__ __forceinline__ void find_bin(const uint32_t* h, uint32_t need, uint3
   for (int i = 0; i < BPT; ++i) {
     const int b = (int)threadIdx.x * BPT + i;
     loc[i] = (b < NB) ? h[b] : 0u;
-  }
-  find_bin_loc<NT, BPT>(loc, need, scratch, found);
-}
-
-// ... with the merged histogram in device memory (read with device-scope
-// 8-byte loads straight into registers)
-template <int NT>
-__device__ __forceinline__ void find_bin_global(const uint32_t* gh, uint32_t need, uint32_t* scratch,
-                                                uint32_t* found) {
-  constexpr int BPT = HIST_BINS / NT;
-  static_assert(BPT >= 2 && BPT % 2 == 0, "two bins per 8-byte load");
-  uint32_t loc[BPT];
-  const uint64_t* p = reinterpret_cast<const uint64_t*>(gh + threadIdx.x * BPT);
-#pragma unroll
-  for (int i = 0; i < BPT / 2; ++i) {
-    const uint64_t w = ld_agent64(p + i);
-    loc[2 * i] = (uint32_t)w;
-    loc[2 * i + 1] = (uint32_t)(w >> 32);
   }
   find_bin_loc<NT, BPT>(loc, need, scratch, found);
 }
