@@ -379,8 +379,8 @@ __device__ __forceinline__ void block_minmax(float& lo, float& hi, float* scratc
 }
 
 // ------------------------------------------------ cross-workgroup barrier
-// A sense-reversing barrier among the P workgroups of one group (state[0..2]:
-// arrival count, sense, exit count; see group_exit).
+// A sense-reversing barrier among the P workgroups of one group (state[0..1]:
+// arrival count, sense).
 //
 // Everything one workgroup hands to another inside a launch (histograms,
 // slots, these counters) is written and read with device-scope atomics
@@ -420,30 +420,6 @@ __device__ __forceinline__ void group_barrier(uint32_t* state, uint32_t P) {
     }
   }
   __syncthreads();
-}
-
-// Leave a group's workspace zero-filled: every workgroup counts itself out in
-// state[2]; the last one clears `words` (per-workgroup slots, which are
-// rewritten before every read and so never cleared in flight), the sense word
-// and the counter.  Nobody waits here.
-template <int NT>
-__device__ __forceinline__ void group_exit(uint32_t* state, uint32_t P, uint32_t* words, uint64_t n_words) {
-  __shared__ uint32_t last_out;
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const uint32_t prev = __hip_atomic_fetch_add(state + 2, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    last_out = (prev == P - 1) ? 1u : 0u;
-  }
-  __syncthreads();
-  if (last_out) {
-    for (uint64_t i = threadIdx.x; i < n_words; i += NT)
-      __hip_atomic_store(words + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (threadIdx.x == 0) {
-      __hip_atomic_store(state + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(state + 2, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  }
 }
 
 __device__ __forceinline__ uint32_t ld_agent(const uint32_t* p) {

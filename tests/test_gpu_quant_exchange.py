@@ -1,0 +1,33 @@
+"""GPU parity of quantization groups spread over several workgroups, bit for
+bit against the CPU oracle: groups in more rounds than are resident at once
+(the min / max slots rotate, or with more than fifteen workgroups per group are
+cleared between barriers), ragged and aligned lengths, minima and maxima of
+either sign of zero; two calls in a row share one workspace."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import TORCH, assert_bits_equal, raw
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_grp,G,dt,bits", [(600, 16385, "f32", 4), (530, 20000, "bf16", 2), (40, 300001, "f32", 3),
+                                             (2, 1000003, "f16", 8), (3, 16384 * 15, "f16", 6),
+                                             (64, 768, "bf16", 4), (5, 2047, "f32", 8), (300, 4, "f16", 1)])
+def test_exchange_parity(tc, orc, n_grp, G, dt, bits):
+    g = torch.Generator().manual_seed(n_grp + G)
+    e = torch.zeros(n_grp * G, device="cuda")
+    eo = np.zeros((n_grp, G), np.float32)
+    for t in range(2):
+        x = torch.randn((n_grp, G), generator=g)
+        x[0] = -0.0 if t else 0.0            # a constant group: lo = hi = +0
+        x = x.to(TORCH[dt])
+        codes, meta = tc.ef_step_quant(x.cuda(), e, bits, n_grp)
+        torch.cuda.synchronize()
+        oc, om, eo = orc.ef_quant(raw(x), dt, eo, n_grp, G, bits)
+        what = f"{n_grp}x{G} {dt} b={bits} step {t}"
+        assert np.array_equal(codes.cpu().numpy().ravel(), np.asarray(oc).view(np.uint8).ravel()), f"codes {what}"
+        assert_bits_equal(raw(meta), np.asarray(om).reshape(n_grp, 2), f"meta {what}")
+        assert_bits_equal(raw(e).reshape(n_grp, G), np.asarray(eo).reshape(n_grp, G), f"e {what}")
+    assert tc.device_errors() == 0
