@@ -1126,8 +1126,8 @@ hipError_t launch(const void* fn, uint32_t grid, uint32_t nt, const GlobalArgs& 
 // (the rest would start only when the first ones have gone through all
 // their tiles, and run the last stretch at a fraction of the occupancy)
 uint32_t resident_grid(const void* fn, uint32_t grid) {
-  int per_cu = 0;
-  if (!fn || hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, G_NT, 0) != hipSuccess || per_cu < 1) return grid;
+  const int per_cu = fn ? resident_per_cu(fn, G_NT) : 0;
+  if (per_cu < 1) return grid;
   return std::max<uint32_t>(1, std::min<uint32_t>(grid, (uint32_t)per_cu * (uint32_t)device_cus()));
 }
 

@@ -501,11 +501,7 @@ SegPlan plan_quant(int dt, uint32_t bits, bool ef, uint64_t n_grp, uint64_t G) {
   p.nt = (G <= (uint64_t)ROW_NT * QVPT) ? ROW_NT : BIG_NT;
   const uint64_t CH = (uint64_t)p.nt * QVPT;
   p.P = (uint32_t)((G + CH - 1) / CH);
-  int occ = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, pick_pack(dt, bits, ef, p.nt), p.nt, 0) != hipSuccess ||
-      occ < 1)
-    occ = 1;
-  const uint64_t cap = (uint64_t)occ * cus;
+  const uint64_t cap = (uint64_t)std::max(1, resident_per_cu(pick_pack(dt, bits, ef, p.nt), p.nt)) * cus;
   p.capacity = cap;
   const uint64_t groups = std::min<uint64_t>(n_grp, std::max<uint64_t>(1, cap / p.P));
   p.n_groups = (uint32_t)groups;

@@ -1368,9 +1368,7 @@ const void* lds_ptr(int sel, int dt) {
 }
 
 int occupancy(const void* fn, int nt) {
-  int blocks = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, fn, nt, 0) != hipSuccess || blocks < 1) blocks = 1;
-  return blocks;
+  return std::max(1, resident_per_cu(fn, nt));
 }
 
 }  // namespace

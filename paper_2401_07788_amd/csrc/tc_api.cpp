@@ -3,10 +3,12 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <initializer_list>
+#include <mutex>
 #include <vector>
 
 #include "../../include/tc.h"
@@ -28,6 +30,34 @@ int device_cus() {
     cached[dev] = n;
   }
   return cached[dev];
+}
+
+// A kernel's occupancy depends on its registers and LDS and on the
+// architecture (this library has one), so it is asked of the runtime once per
+// kernel: asked on every call, a plan of the several-workgroup engine made
+// four such queries.  Entries are only ever added, the value before the key.
+int resident_per_cu(const void* fn, int nt) {
+  constexpr unsigned SLOTS = 2048, PROBES = 32;
+  static struct { std::atomic<const void*> fn; std::atomic<int> n; } table[SLOTS];
+  unsigned h = (unsigned)(((uintptr_t)fn >> 3) * 0x9E3779B97F4A7C15ull >> 40);
+  unsigned free_slot = SLOTS;
+  for (unsigned p = 0; p < PROBES; ++p) {
+    const unsigned i = (h + p) % SLOTS;
+    const void* k = table[i].fn.load(std::memory_order_acquire);
+    if (k == fn) return table[i].n.load(std::memory_order_relaxed);
+    if (!k) { free_slot = i; break; }
+  }
+  int n = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, nt, 0) != hipSuccess || n < 1) return 0;
+  if (free_slot < SLOTS) {
+    static std::mutex m;
+    std::lock_guard<std::mutex> g(m);
+    if (!table[free_slot].fn.load(std::memory_order_relaxed)) {
+      table[free_slot].n.store(n, std::memory_order_relaxed);
+      table[free_slot].fn.store(fn, std::memory_order_release);
+    }
+  }
+  return n;
 }
 
 }  // namespace tc

@@ -179,6 +179,9 @@ hipError_t errors_global_raise(uint32_t bits);
 
 // device properties (cached per device)
 int device_cus();
+// workgroups of kernel fn (always launched with nt threads) one compute unit
+// holds, 0 when the runtime does not say; asked once per kernel
+int resident_per_cu(const void* fn, int nt);
 
 // ---- library-owned scratch of the allocation-free entry point (k_scratch.hip)
 constexpr uint64_t NOALLOC_SCRATCH_BYTES = 4ull << 20;    // TC_NOALLOC_SCRATCH_BYTES

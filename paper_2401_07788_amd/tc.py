@@ -82,14 +82,14 @@ EXPORTS = {
     "tc_topk_compress": (C.c_int, [C.POINTER(Codec), C.c_void_p, C.c_int, C.POINTER(Payload), C.c_void_p,
                                    C.c_size_t, C.c_void_p]),
     "tc_topk_decompress": (C.c_int, [C.POINTER(Codec), C.POINTER(Payload), C.c_void_p, C.c_int, C.c_void_p]),
-    "tc_topk_gather": (C.c_int, [C.POINTER(Codec), C.POINTER(Payload), C.c_void_p, C.c_int, C.POINTER(C.c_float),
+    "tc_topk_gather": (C.c_int, [C.POINTER(Codec), C.POINTER(Payload), C.c_void_p, C.c_int, C.c_void_p,
                                  C.c_void_p, C.c_void_p]),
     "tc_quant_pack": (C.c_int, [C.POINTER(Codec), C.c_void_p, C.c_int, C.POINTER(Payload), C.c_void_p,
                                 C.c_size_t, C.c_void_p]),
     "tc_quant_unpack": (C.c_int, [C.POINTER(Codec), C.POINTER(Payload), C.c_void_p, C.c_int, C.c_void_p]),
-    "tc_ef_step": (C.c_int, [C.POINTER(Codec), C.c_void_p, C.c_int, C.POINTER(C.c_float), C.POINTER(Payload),
+    "tc_ef_step": (C.c_int, [C.POINTER(Codec), C.c_void_p, C.c_int, C.c_void_p, C.POINTER(Payload),
                              C.c_void_p, C.c_size_t, C.c_void_p]),
-    "tc_efmix_step": (C.c_int, [C.POINTER(Codec), C.c_void_p, C.c_int, C.POINTER(C.c_float), C.POINTER(Payload),
+    "tc_efmix_step": (C.c_int, [C.POINTER(Codec), C.c_void_p, C.c_int, C.c_void_p, C.POINTER(Payload),
                                 C.POINTER(Payload), C.c_void_p]),
     "tc_efmix_reconstruct": (C.c_int, [C.POINTER(Codec), C.POINTER(Payload), C.POINTER(Payload), C.c_void_p, C.c_int,
                                        C.c_void_p]),
@@ -153,11 +153,19 @@ def _check(rc: int, where: str):
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    # (a plain int: the prototypes and Payload's fields convert it)
+    return None if t is None else t.data_ptr()
+
+
+# the current stream's handle as an int: a Stream object per call costs ten
+# times as much
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(device):
-    return C.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    if _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 def _need_gpu(*ts):
@@ -173,14 +181,14 @@ def _check_topk_payload(pl, n_seg: int, k: int, seg_len: int, val_dtype, device,
                         need_val: bool = True):
     """a TopK payload the caller supplies must have exactly the shapes the
     kernels write or read: the C entry points only see pointers"""
-    if pl.idx is None or tuple(pl.idx.shape) != (n_seg, k) or pl.idx.dtype != torch.int32:
+    if pl.idx is None or pl.idx.shape != (n_seg, k) or pl.idx.dtype != torch.int32:
         raise ValueError(f"{what}.idx must be int32 [{n_seg}, {k}]")
     if need_val:
-        if pl.val is None or tuple(pl.val.shape) != (n_seg, k):
+        if pl.val is None or pl.val.shape != (n_seg, k):
             raise ValueError(f"{what}.val must be [{n_seg}, {k}]")
         if pl.val.dtype != val_dtype:
             raise TypeError(f"{what}.val must be {val_dtype}")
-    if pl.blk is not None and (tuple(pl.blk.shape) != (n_seg, n_blocks(seg_len) + 1) or pl.blk.dtype != torch.int32):
+    if pl.blk is not None and (pl.blk.shape != (n_seg, n_blocks(seg_len) + 1) or pl.blk.dtype != torch.int32):
         raise ValueError(f"{what}.blk must be int32 [{n_seg}, {n_blocks(seg_len) + 1}]")
     for t in (pl.idx, pl.val if need_val else None, pl.blk):
         if t is not None and (t.device != device or not t.is_contiguous()):
@@ -199,6 +207,29 @@ def _dt(t) -> int:
         return _DT[t.dtype]
     except KeyError:
         raise TypeError(f"unsupported dtype {t.dtype}") from None
+
+
+class _Plan:
+    """a codec, its reference and (once asked for) its workspace's size: what
+    every call of one shape shares"""
+    __slots__ = ("codec", "ref", "ws_bytes")
+
+    def __init__(self, c):
+        self.codec, self.ref, self.ws_bytes = c, C.byref(c), None
+
+
+_plans = {}
+_PLANS_MAX = 1024
+
+
+def _plan(kind: int, device, n_seg: int, seg_len: int, k: int = 0, bits: int = 0, wire: int = TC_F32) -> _Plan:
+    key = (kind, device.index, n_seg, seg_len, k, bits, wire)
+    p = _plans.get(key)
+    if p is None:
+        if len(_plans) >= _PLANS_MAX:
+            _plans.clear()
+        p = _plans[key] = _Plan(codec(kind, n_seg, seg_len, k, bits, wire))
+    return p
 
 
 def codec(kind: int, n_seg: int, seg_len: int, k: int = 0, bits: int = 0, wire: int = TC_F32) -> Codec:
@@ -256,25 +287,35 @@ def raise_device_errors(bits: int) -> None:
     _check(lib().tc_raise_device_errors(int(bits)), "tc_raise_device_errors")
 
 
-def _ws_args(c, device, ws):
-    if ws is None:
-        ws = workspace(c, device)
-    return (_ptr(ws), 0 if ws is None else ws.numel() * ws.element_size())
+def _ws_args(p, device, ws, stream):
+    """pointer and size of the given workspace, else of the stream's own"""
+    if ws is not None:
+        return ws.data_ptr(), ws.numel() * ws.element_size()
+    n = p.ws_bytes
+    if n is None:
+        n = p.ws_bytes = workspace_bytes(p.codec)
+    if n == 0:
+        return None, 0
+    ws = _ws_cache.get((device.index, stream))
+    if ws is None or ws.numel() < n:
+        ws = workspace(p.codec, device)
+    return ws.data_ptr(), ws.numel()
 
 
 # --------------------------------------------------------------------- TopK
 def topk_compress(x: torch.Tensor, k: int, n_seg: int, ws=None, out: TopkPayload = None, blk: bool = True):
     """TopK per segment of x viewed as [n_seg, seg_len] -> TopkPayload"""
     L = _segments(x, n_seg)
-    c = codec(TC_TOPK, n_seg, L, k, wire=_dt(x))
+    c = _plan(TC_TOPK, x.device, n_seg, L, k, wire=_dt(x))
     if out is not None:
         _check_topk_payload(out, n_seg, k, L, x.dtype, x.device, "out")
     _need_gpu(x)
     if out is None:
         out = empty_topk_payload(n_seg, L, k, x.dtype, x.device, blk)
     p = Payload(_ptr(out.idx), _ptr(out.val), None, None, _ptr(out.blk))
-    w, wn = _ws_args(c, x.device, ws)
-    _check(lib().tc_topk_compress(C.byref(c), _ptr(x), _dt(x), C.byref(p), w, wn, _stream(x.device)),
+    st = _stream(x.device)
+    w, wn = _ws_args(c, x.device, ws, st)
+    _check(lib().tc_topk_compress(c.ref, _ptr(x), _dt(x), C.byref(p), w, wn, st),
            "tc_topk_compress")
     return out
 
@@ -291,10 +332,10 @@ def topk_decompress(pl: TopkPayload, seg_len: int, out_dtype=None, use_blk: bool
         out_dtype = out.dtype
     out_dtype = out_dtype or pl.val.dtype
     _need_gpu(pl.idx, pl.val, pl.blk, out)
-    c = codec(TC_TOPK, n_seg, seg_len, k, wire=_dt(pl.val))
+    c = _plan(TC_TOPK, pl.idx.device, n_seg, seg_len, k, wire=_dt(pl.val))
     y = out if out is not None else torch.empty((n_seg, seg_len), dtype=out_dtype, device=pl.idx.device)
     p = Payload(_ptr(pl.idx), _ptr(pl.val), None, None, _ptr(pl.blk) if use_blk else None)
-    _check(lib().tc_topk_decompress(C.byref(c), C.byref(p), _ptr(y), _DT[out_dtype], _stream(pl.idx.device)),
+    _check(lib().tc_topk_decompress(c.ref, C.byref(p), _ptr(y), _DT[out_dtype], _stream(pl.idx.device)),
            "tc_topk_decompress")
     return y
 
@@ -315,10 +356,10 @@ def topk_gather(pl: TopkPayload, x: torch.Tensor, e: torch.Tensor = None, use_bl
         raise ValueError(f"out must be {x.dtype} [{n_seg}, {k}]")
     _need_gpu(pl.idx, pl.blk, x, e, out)
     val = out if out is not None else torch.empty((n_seg, k), dtype=x.dtype, device=x.device)
-    c = codec(TC_TOPK, n_seg, L, k, wire=_dt(x))
+    c = _plan(TC_TOPK, x.device, n_seg, L, k, wire=_dt(x))
     p = Payload(_ptr(pl.idx), None, None, None, _ptr(pl.blk) if use_blk else None)
-    ep = None if e is None else C.cast(e.data_ptr(), C.POINTER(C.c_float))
-    _check(lib().tc_topk_gather(C.byref(c), C.byref(p), _ptr(x), _dt(x), ep, _ptr(val), _stream(x.device)),
+    ep = None if e is None else e.data_ptr()
+    _check(lib().tc_topk_gather(c.ref, C.byref(p), _ptr(x), _dt(x), ep, _ptr(val), _stream(x.device)),
            "tc_topk_gather")
     return val
 
@@ -328,12 +369,13 @@ def quant_pack(x: torch.Tensor, bits: int, n_grp: int, ws=None):
     """min-max quantization per group -> (codes uint8 [n_grp, group_bytes], meta f32 [n_grp, 2])"""
     _need_gpu(x)
     G = _segments(x, n_grp)
-    c = codec(TC_QUANT, n_grp, G, bits=bits, wire=_dt(x))
+    c = _plan(TC_QUANT, x.device, n_grp, G, bits=bits, wire=_dt(x))
     codes = torch.empty((n_grp, quant_group_bytes(G, bits)), dtype=torch.uint8, device=x.device)
     meta = torch.empty((n_grp, 2), dtype=torch.float32, device=x.device)
     p = Payload(None, None, _ptr(codes), _ptr(meta), None)
-    w, wn = _ws_args(c, x.device, ws)
-    _check(lib().tc_quant_pack(C.byref(c), _ptr(x), _dt(x), C.byref(p), w, wn, _stream(x.device)), "tc_quant_pack")
+    st = _stream(x.device)
+    w, wn = _ws_args(c, x.device, ws, st)
+    _check(lib().tc_quant_pack(c.ref, _ptr(x), _dt(x), C.byref(p), w, wn, st), "tc_quant_pack")
     return codes, meta
 
 
@@ -350,10 +392,10 @@ def quant_unpack(codes: torch.Tensor, meta: torch.Tensor, grp_len: int, bits: in
             raise ValueError("out has the wrong element count")
         out_dtype = out.dtype
     _need_gpu(codes, meta, out)
-    c = codec(TC_QUANT, n_grp, grp_len, bits=bits, wire=_DT[out_dtype])
+    c = _plan(TC_QUANT, codes.device, n_grp, grp_len, bits=bits, wire=_DT[out_dtype])
     y = out if out is not None else torch.empty((n_grp, grp_len), dtype=out_dtype, device=codes.device)
     p = Payload(None, None, _ptr(codes), _ptr(meta), None)
-    _check(lib().tc_quant_unpack(C.byref(c), C.byref(p), _ptr(y), _DT[out_dtype], _stream(codes.device)),
+    _check(lib().tc_quant_unpack(c.ref, C.byref(p), _ptr(y), _DT[out_dtype], _stream(codes.device)),
            "tc_quant_unpack")
     return y
 
@@ -365,16 +407,17 @@ def ef_step_topk(x: torch.Tensor, e: torch.Tensor, k: int, n_seg: int, ws=None, 
     if e.dtype != torch.float32 or e.numel() != x.numel():
         raise ValueError("e must be float32 with x's element count")
     L = _segments(x, n_seg)
-    c = codec(TC_TOPK, n_seg, L, k, wire=_dt(x))
+    c = _plan(TC_TOPK, x.device, n_seg, L, k, wire=_dt(x))
     if out is not None:
         _check_topk_payload(out, n_seg, k, L, x.dtype, x.device, "out")
     _need_gpu(x, e)
     if out is None:
         out = empty_topk_payload(n_seg, L, k, x.dtype, x.device, blk)
     p = Payload(_ptr(out.idx), _ptr(out.val), None, None, _ptr(out.blk))
-    w, wn = _ws_args(c, x.device, ws)
-    _check(lib().tc_ef_step(C.byref(c), _ptr(x), _dt(x), C.cast(e.data_ptr(), C.POINTER(C.c_float)), C.byref(p),
-                            w, wn, _stream(x.device)), "tc_ef_step")
+    st = _stream(x.device)
+    w, wn = _ws_args(c, x.device, ws, st)
+    _check(lib().tc_ef_step(c.ref, _ptr(x), _dt(x), e.data_ptr(), C.byref(p),
+                            w, wn, st), "tc_ef_step")
     return out
 
 
@@ -385,7 +428,7 @@ def ef_step_quant(x: torch.Tensor, e: torch.Tensor, bits: int, n_grp: int, ws=No
     if e.dtype != torch.float32 or e.numel() != x.numel():
         raise ValueError("e must be float32 with x's element count")
     G = _segments(x, n_grp)
-    c = codec(TC_QUANT, n_grp, G, bits=bits, wire=_dt(x))
+    c = _plan(TC_QUANT, x.device, n_grp, G, bits=bits, wire=_dt(x))
     if out is not None:
         codes, meta = out
         _need_gpu(codes, meta)
@@ -395,9 +438,10 @@ def ef_step_quant(x: torch.Tensor, e: torch.Tensor, bits: int, n_grp: int, ws=No
         codes = torch.empty((n_grp, quant_group_bytes(G, bits)), dtype=torch.uint8, device=x.device)
         meta = torch.empty((n_grp, 2), dtype=torch.float32, device=x.device)
     p = Payload(None, None, _ptr(codes), _ptr(meta), None)
-    w, wn = _ws_args(c, x.device, ws)
-    _check(lib().tc_ef_step(C.byref(c), _ptr(x), _dt(x), C.cast(e.data_ptr(), C.POINTER(C.c_float)), C.byref(p),
-                            w, wn, _stream(x.device)), "tc_ef_step")
+    st = _stream(x.device)
+    w, wn = _ws_args(c, x.device, ws, st)
+    _check(lib().tc_ef_step(c.ref, _ptr(x), _dt(x), e.data_ptr(), C.byref(p),
+                            w, wn, st), "tc_ef_step")
     return codes, meta
 
 
@@ -442,7 +486,7 @@ def ef_step_topk_quant(x: torch.Tensor, e: torch.Tensor, k: int, bits: int, n_se
     if e.dtype != torch.float32 or e.numel() != x.numel():
         raise ValueError("e must be float32 with x's element count")
     L = _segments(x, n_seg)
-    c = codec(TC_TOPK_QUANT, n_seg, L, k, bits=bits, wire=_dt(x))
+    c = _plan(TC_TOPK_QUANT, x.device, n_seg, L, k, bits, wire=_dt(x))
     dev = x.device
     if out is not None:
         _check_topk_quant_payload(out, n_seg, k, L, bits, dev, "out")
@@ -450,9 +494,10 @@ def ef_step_topk_quant(x: torch.Tensor, e: torch.Tensor, k: int, bits: int, n_se
     if out is None:
         out = empty_topk_quant_payload(n_seg, L, k, bits, dev, blk)
     p = Payload(_ptr(out.idx), None, _ptr(out.codes), _ptr(out.meta), _ptr(out.blk))
-    w, wn = _ws_args(c, dev, ws)
-    _check(lib().tc_ef_step(C.byref(c), _ptr(x), _dt(x), C.cast(e.data_ptr(), C.POINTER(C.c_float)), C.byref(p),
-                            w, wn, _stream(dev)), "tc_ef_step")
+    st = _stream(dev)
+    w, wn = _ws_args(c, dev, ws, st)
+    _check(lib().tc_ef_step(c.ref, _ptr(x), _dt(x), e.data_ptr(), C.byref(p),
+                            w, wn, st), "tc_ef_step")
     return out
 
 
@@ -468,10 +513,10 @@ def topk_quant_decompress(pl: TopkQuantPayload, seg_len: int, out_dtype=torch.fl
             raise ValueError("out has the wrong element count")
         out_dtype = out.dtype
     _need_gpu(pl.idx, pl.codes, pl.meta, pl.blk, out)
-    c = codec(TC_TOPK_QUANT, n_seg, seg_len, k, bits=pl.bits, wire=_DT[out_dtype])
+    c = _plan(TC_TOPK_QUANT, pl.idx.device, n_seg, seg_len, k, pl.bits, wire=_DT[out_dtype])
     y = out if out is not None else torch.empty((n_seg, seg_len), dtype=out_dtype, device=pl.idx.device)
     p = Payload(_ptr(pl.idx), None, _ptr(pl.codes), _ptr(pl.meta), _ptr(pl.blk) if use_blk else None)
-    _check(lib().tc_topk_decompress(C.byref(c), C.byref(p), _ptr(y), _DT[out_dtype], _stream(pl.idx.device)),
+    _check(lib().tc_topk_decompress(c.ref, C.byref(p), _ptr(y), _DT[out_dtype], _stream(pl.idx.device)),
            "tc_topk_decompress")
     return y
 
@@ -492,7 +537,7 @@ def efmix_step(x: torch.Tensor, e: torch.Tensor, k: int, n_seg: int, out=None, b
         raise ValueError("e must be float32 with x's element count")
     L = _segments(x, n_seg)
     kx, ke = efmix_counts(k)
-    c = codec(TC_TOPK, n_seg, L, k, wire=_dt(x))
+    c = _plan(TC_TOPK, x.device, n_seg, L, k, wire=_dt(x))
     if out is not None:
         _check_topk_payload(out[0], n_seg, kx, L, x.dtype, x.device, "out[0]")
         _check_topk_payload(out[1], n_seg, ke, L, x.dtype, x.device, "out[1]")
@@ -503,7 +548,7 @@ def efmix_step(x: torch.Tensor, e: torch.Tensor, k: int, n_seg: int, out=None, b
     px, pe = out
     a = Payload(_ptr(px.idx), _ptr(px.val), None, None, _ptr(px.blk))
     b = Payload(_ptr(pe.idx), _ptr(pe.val), None, None, _ptr(pe.blk))
-    _check(lib().tc_efmix_step(C.byref(c), _ptr(x), _dt(x), C.cast(e.data_ptr(), C.POINTER(C.c_float)),
+    _check(lib().tc_efmix_step(c.ref, _ptr(x), _dt(x), e.data_ptr(),
                                C.byref(a), C.byref(b), _stream(x.device)), "tc_efmix_step")
     return out
 
@@ -525,11 +570,11 @@ def efmix_reconstruct(px: TopkPayload, pe: TopkPayload, seg_len: int, out_dtype=
         out_dtype = out.dtype
     out_dtype = out_dtype or px.val.dtype
     _need_gpu(px.idx, px.val, pe.idx, pe.val, out)
-    c = codec(TC_TOPK, n_seg, seg_len, kx + ke, wire=_dt(px.val))
+    c = _plan(TC_TOPK, px.idx.device, n_seg, seg_len, kx + ke, wire=_dt(px.val))
     y = out if out is not None else torch.empty((n_seg, seg_len), dtype=out_dtype, device=px.idx.device)
     a = Payload(_ptr(px.idx), _ptr(px.val), None, None, _ptr(px.blk) if use_blk else None)
     b = Payload(_ptr(pe.idx), _ptr(pe.val), None, None, _ptr(pe.blk) if use_blk else None)
-    _check(lib().tc_efmix_reconstruct(C.byref(c), C.byref(a), C.byref(b), _ptr(y), _DT[out_dtype],
+    _check(lib().tc_efmix_reconstruct(c.ref, C.byref(a), C.byref(b), _ptr(y), _DT[out_dtype],
                                       _stream(px.idx.device)), "tc_efmix_reconstruct")
     return y
 
@@ -547,7 +592,7 @@ def _aqsgd_prepare(a, m, ids, k, out, blk):
     L = m.shape[1]
     if a.numel() != n_ids * L:
         raise ValueError(f"a must hold n_ids * seg_len = {n_ids} * {L} elements")
-    c = codec(TC_TOPK, n_ids, L, k, wire=_dt(m))
+    c = _plan(TC_TOPK, a.device, n_ids, L, k, wire=_dt(m))
     if out is not None:
         _check_topk_payload(out, n_ids, k, L, a.dtype, a.device, "out")
     _need_gpu(a, m, ids)
@@ -560,9 +605,10 @@ def aqsgd_step(a: torch.Tensor, m: torch.Tensor, ids: torch.Tensor, k: int, ws=N
                blk: bool = True):
     """sender: d = a - m[ids]; send TopK(d); m[ids] += sent.  m is updated in place."""
     c, n_ids, out, p = _aqsgd_prepare(a, m, ids, k, out, blk)
-    w, wn = _ws_args(c, a.device, ws)
-    _check(lib().tc_aqsgd_step(C.byref(c), _ptr(a), _dt(a), _ptr(m), m.shape[0], _ptr(ids), n_ids, C.byref(p),
-                               w, wn, _stream(a.device)), "tc_aqsgd_step")
+    st = _stream(a.device)
+    w, wn = _ws_args(c, a.device, ws, st)
+    _check(lib().tc_aqsgd_step(c.ref, _ptr(a), _dt(a), _ptr(m), m.shape[0], _ptr(ids), n_ids, C.byref(p),
+                               w, wn, st), "tc_aqsgd_step")
     return out
 
 
@@ -575,7 +621,7 @@ def aqsgd_step_noalloc(a: torch.Tensor, m: torch.Tensor, ids: torch.Tensor, k: i
     the library's own, shared by every call on the device); pass `out` to keep
     this call free of allocations on the Python side too."""
     c, n_ids, out, p = _aqsgd_prepare(a, m, ids, k, out, blk)
-    _check(lib().tc_aqsgd_step_noalloc(C.byref(c), _ptr(a), _dt(a), _ptr(m), m.shape[0], _ptr(ids), n_ids,
+    _check(lib().tc_aqsgd_step_noalloc(c.ref, _ptr(a), _dt(a), _ptr(m), m.shape[0], _ptr(ids), n_ids,
                                        C.byref(p), _stream(a.device)), "tc_aqsgd_step_noalloc")
     return out
 
@@ -621,9 +667,9 @@ def aqsgd_reconstruct(pl: TopkPayload, m_r: torch.Tensor, ids: torch.Tensor, out
     if out is not None and (out.numel() != n_ids * L or out.dtype != m_r.dtype):
         raise ValueError(f"out must be {m_r.dtype} with {n_ids} * {L} elements")
     _need_gpu(pl.idx, pl.val, pl.blk, m_r, ids, out)
-    c = codec(TC_TOPK, n_ids, L, k, wire=_dt(m_r))
+    c = _plan(TC_TOPK, m_r.device, n_ids, L, k, wire=_dt(m_r))
     a_hat = torch.empty((n_ids, L), dtype=m_r.dtype, device=m_r.device) if out is None else out
     p = Payload(_ptr(pl.idx), _ptr(pl.val), None, None, _ptr(pl.blk) if use_blk else None)
-    _check(lib().tc_aqsgd_reconstruct(C.byref(c), C.byref(p), _ptr(m_r), _dt(m_r), m_r.shape[0], _ptr(ids), n_ids,
+    _check(lib().tc_aqsgd_reconstruct(c.ref, C.byref(p), _ptr(m_r), _dt(m_r), m_r.shape[0], _ptr(ids), n_ids,
                                       _ptr(a_hat), _stream(m_r.device)), "tc_aqsgd_reconstruct")
     return a_hat
