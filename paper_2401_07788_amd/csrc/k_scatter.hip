@@ -791,9 +791,13 @@ __global__ __launch_bounds__(SC_NT) void k_gather_ef(GatherArgs a) {
 
 namespace {
 
+// A workgroup per chunk: its chain (range, entries, LDS, store) runs once, and
+// the compute units overlap the chains of what they hold.  The large language
+// model's receiver (32,768 chunks, 2^27 bfloat16, TopK 10 % at 4 bits) goes from
+// 114.5 to 89 us (3.7 TB/s) against workgroups that loop over 16 chunks each.
 uint32_t scatter_grid(uint64_t n_seg, uint64_t L) {
   const uint64_t work = n_seg * ((L + SC_CH - 1) / SC_CH);
-  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(work, (uint64_t)device_cus() * 8));
+  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(work, 1u << 20));
 }
 
 template <typename WireT>
