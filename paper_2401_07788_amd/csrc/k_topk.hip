@@ -16,8 +16,8 @@
 //
 // Three engines:
 //   k_topk_row : one wavefront per segment of up to 2048 elements (token
-//                rows); radix select over 8-bit digits with a wavefront-
-//                private LDS histogram, one wavefront scan per digit.
+//                rows), in registers; the threshold from a window of fine
+//                bins around a guess.
 //   k_topk_lds : one 1024-thread workgroup per segment of up to 32,768
 //                elements (per-sample tensors), the segment held in LDS.
 //   k_topk_grp : P workgroups of 512 threads per segment (long samples,
@@ -48,86 +48,257 @@ __device__ __forceinline__ void map_wg(uint32_t wg, uint32_t grid, uint32_t P, u
 }
 
 // ------------------------------------------------------------- row engine
-template <typename InT, int SEL, int VPT>
+// Piece p of lane l is elements p * 256 + 4 l .. + 3: every wavefront access
+// covers whole lines, and index order is (piece, lane, element).  A piece
+// past the row's end holds +0, which ranks after every element.
+constexpr uint32_t ROW_PIECE = WAVE * 4;   // elements of one piece over the wavefront
+
+// LDS of one row: its kept entries in index order (16-bit values share the
+// index's word), and a word per lane for the entries it does not keep
+template <typename Raw, int NP>
+struct RowStage {
+  union {
+    __attribute__((aligned(16))) uint32_t hist[RW_WORDS];   // the selection's
+    uint32_t w[ROW_PIECE * NP + WAVE];
+  };
+  uint16_t i[sizeof(Raw) == 4 ? ROW_PIECE * NP + WAVE : 1];
+};
+
+// Exclusive prefix sums, in index order, of one count per piece (0 to 4 per
+// lane, 256 per piece and wavefront): three pieces' counts share a word.
+template <int NP>
+__device__ __forceinline__ uint32_t row_scan(const uint32_t (&n)[NP], uint32_t (&ex)[NP]) {
+  uint32_t base = 0;
+#pragma unroll
+  for (int p0 = 0; p0 < NP; p0 += 3) {
+    uint32_t w = 0;
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (p0 + q < NP) w |= n[p0 + q] << (10 * q);
+    const uint32_t incl = wave_incl_scan(w);
+    const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
+    const uint32_t x = incl - w;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      if (p0 + q < NP) {
+        ex[p0 + q] = base + ((x >> (10 * q)) & 0x3FFu);
+        base += (tot >> (10 * q)) & 0x3FFu;
+      }
+    }
+  }
+  return base;
+}
+
+// One wavefront per row.  What bounds it is instruction issue (four rows share
+// a SIMD) and, under that, memory: so flags are bit masks, no branch stands
+// per element, and the payload leaves from LDS in lane-consecutive stores.
+// 4096 rows of 768 bfloat16 with EF, 10 % kept: 12.0 us when a lane held
+// consecutive elements and the threshold came from digit passes, 8.7 now (3.8
+// TB/s); of a wavefront's 4.2 us the loads take 1.0, the selection 1.5.
+template <typename InT, int SEL, int NP>
 __global__ __launch_bounds__(WAVE) void k_topk_row(TopkArgs a) {
   using R = typename Elem<InT>::raw;
-  __shared__ uint32_t scratch[2];
-  __shared__ __attribute__((aligned(16))) uint32_t hist[RADIX_CP * RADIX_HS];
+  constexpr int V = 4 * NP;
+  __shared__ RowStage<R, NP> st;
+  const uint32_t L = (uint32_t)a.L, k = (uint32_t)a.k;
+  const float lL = __builtin_amdgcn_logf((float)L), lk = __builtin_amdgcn_logf((float)max(k, 1u));
+  const RowLogs lg{lk, lL, 0.95f * 0.6931472f * __builtin_amdgcn_logf((float)L * __builtin_amdgcn_rcpf((float)max(k, 1u)) + 0.15f)};
+  const float rl = __builtin_amdgcn_rcpf((float)L);
+  const bool vec = (((uintptr_t)a.x | (uintptr_t)a.e | (uintptr_t)a.m) & 15u) == 0 && (L % 4u) == 0;
   for (uint64_t seg = blockIdx.x; seg < a.n_seg; seg += gridDim.x) {
-    const uint64_t c0 = (uint64_t)threadIdx.x * VPT;
-    const int nv = (int)min((uint64_t)VPT, sat_sub(a.L, c0));
-
-    // ---- producer: the vector to compress, in binary32
-    float v[VPT];
-    R mr[VPT];                 // AQSGD: the buffer row, kept for the update
-    uint64_t mrow = 0;
+    // (what follows from the lane is computed where it is used, not ahead of
+    // the loop, which most launches go through once: it would not fit the
+    // registers)
+    uint32_t lane = threadIdx.x;
+    asm volatile("" : "+v"(lane));
+    R* mrow = nullptr;
     if constexpr (SEL == SEL_AQSGD) {
       const int64_t id = load_uniform(a.ids + seg);
       if (id < 0 || (uint64_t)id >= a.n_samples) {
-        if (threadIdx.x == 0) raise_error(KERR_BAD_ID);
+        if (lane == 0) raise_error(KERR_BAD_ID);
         continue;
       }
-      mrow = (uint64_t)id * a.L;
+      mrow = (R*)a.m + (uint64_t)id * a.L;
     }
-    {
-      R xr[VPT];
-      const uint64_t off = seg * a.L + c0;
-      if (nv > 0) load_run_partial<R, VPT, true>((const R*)a.x + off, nv, R{}, xr);
-      if constexpr (SEL == SEL_EF) {
-        float er[VPT];
-        if (nv > 0) load_run_partial<float, VPT, true>(a.e + off, nv, 0.0f, er);
+    const R* const xs = (const R*)a.x + seg * a.L;
+    float* const es = (SEL == SEL_EF) ? a.e + seg * a.L : nullptr;
+
+    // ---- producer: the vector to compress, in binary32
+    R xr[NP][4], mr[NP][4];      // (AQSGD: the buffer row, kept for the update)
+    float er[NP][4];
+    if (vec) {
+      // a piece lies wholly inside or wholly past the row; one past it reads
+      // the row's first piece, unused: no branch stands between the loads
 #pragma unroll
-        for (int i = 0; i < VPT; ++i) v[i] = (i < nv) ? Elem<InT>::up(xr[i]) + er[i] : 0.0f;
-      } else if constexpr (SEL == SEL_AQSGD) {
-        if (nv > 0) load_run_partial<R, VPT, true>((const R*)a.m + mrow + c0, nv, R{}, mr);
+      for (int p = 0; p < NP; ++p) {
+        const uint32_t o = (uint32_t)p * ROW_PIECE + lane * 4u, at = (o < L) ? o : 0u;
+        load_piece<R, true>(xs + at, xr[p]);
+        if constexpr (SEL == SEL_EF) load_piece<float, true>(es + at, er[p]);
+        if constexpr (SEL == SEL_AQSGD) load_piece<R, true>(mrow + at, mr[p]);
+      }
+    } else if (L >= 4u) {
+      // the piece across the row's end reads the last four elements
 #pragma unroll
-        for (int i = 0; i < VPT; ++i) v[i] = (i < nv) ? Elem<InT>::up(xr[i]) - Elem<InT>::up(mr[i]) : 0.0f;
-      } else {
+      for (int p = 0; p < NP; ++p) {
+        const uint32_t at = min((uint32_t)p * ROW_PIECE + lane * 4u, L - 4u);
+        load_piece_any<R>(xs + at, xr[p]);
+        if constexpr (SEL == SEL_EF) load_piece_any<float>(es + at, er[p]);
+        if constexpr (SEL == SEL_AQSGD) load_piece_any<R>(mrow + at, mr[p]);
+      }
+      // ... and moves those it holds to the front
+      auto front = [&](auto& w, uint32_t sh) {
+        if (sh & 1u) { w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; }
+        if (sh & 2u) { w[0] = w[2]; w[1] = w[3]; }
+      };
 #pragma unroll
-        for (int i = 0; i < VPT; ++i) v[i] = (i < nv) ? Elem<InT>::up(xr[i]) : 0.0f;
+      for (int p = 0; p < NP; ++p) {
+        const uint32_t o = (uint32_t)p * ROW_PIECE + lane * 4u;
+        if ((uint32_t)p * ROW_PIECE + ROW_PIECE <= L) continue;   // (no lane's piece is cut)
+        const uint32_t sh = o - min(o, L - 4u);
+        front(xr[p], sh);
+        if constexpr (SEL == SEL_EF) front(er[p], sh);
+        if constexpr (SEL == SEL_AQSGD) front(mr[p], sh);
+      }
+    } else {
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t at = min((uint32_t)p * ROW_PIECE + lane * 4u + (uint32_t)i, L - 1u);
+          xr[p][i] = xs[at];
+          if constexpr (SEL == SEL_EF) er[p][i] = es[at];
+          if constexpr (SEL == SEL_AQSGD) mr[p][i] = mrow[at];
+        }
+    }
+    float v[NP][4], sum = 0.0f;
+    uint32_t key[V], bits = 0;
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float x = Elem<InT>::up(xr[p][i]);
+        if constexpr (SEL == SEL_EF) x = x + er[p][i];
+        if constexpr (SEL == SEL_AQSGD) x = x - Elem<InT>::up(mr[p][i]);
+        v[p][i] = ((uint32_t)p * ROW_PIECE + lane * 4u + (uint32_t)i < L) ? x : 0.0f;
+        const uint32_t kk = mag_key(v[p][i]);
+        key[4 * p + i] = kk;
+        sum += __uint_as_float(kk);
+        bits |= kk;
+      }
+
+    // ---- selection
+    // ---- kept entries: a 4-bit mask per piece
+    uint32_t km[NP] = {}, n[NP] = {}, ex[NP] = {};
+    if (k > 0u) {
+      // the bits every key lacks: 16-bit inputs leave 13 or 16, and so may
+      // differences of them
+      uint32_t tz = 0u;
+      if constexpr (sizeof(R) == 2) {
+        if constexpr (SEL == SEL_PLAIN) tz = std::is_same<InT, bf16_t>::value ? 16u : 13u;
+        if constexpr (SEL == SEL_AQSGD) tz = (uint32_t)__builtin_ctz(wave_or(bits) | (1u << RW_SHIFT));
+      }
+      const uint32_t T = wave_select_key<V>(key, L, k, tz, wave_fsum(sum) * rl, lg, st.hist);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) km[p] |= (1u ^ gt31(T, key[4 * p + i])) << i;
+        n[p] = (uint32_t)__builtin_popcount(km[p]);
+      }
+      const uint32_t total = row_scan<NP>(n, ex);
+      if (total != k) {
+        // more keys equal to T than are kept: the lowest-indexed ones are
+        uint32_t em[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+          em[p] = 0u;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) em[p] |= eq31(key[4 * p + i], T) << i;
+          n[p] = (uint32_t)__builtin_popcount(em[p]);
+        }
+        const uint32_t ties = row_scan<NP>(n, ex);
+        const uint32_t r = k - min(k, total - ties);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+          uint32_t left = sat_sub(r, ex[p]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const uint32_t tie = (em[p] >> i) & 1u, on = tie & gt31(left, 0u);
+            km[p] &= ~((tie ^ on) << i);
+            left -= on;
+          }
+          n[p] = (uint32_t)__builtin_popcount(km[p]);
+        }
+        if (row_scan<NP>(n, ex) != k && lane == 0) raise_error(KERR_INTERNAL);
       }
     }
-    uint32_t key[VPT];
-#pragma unroll
-    for (int i = 0; i < VPT; ++i) key[i] = mag_key(v[i]);
 
-    SelResult sr;
-    if (a.k == 0) { sr.T = 0xFFFFFFFFu; sr.r = 0; sr.gt_before = 0; sr.eq_before = 0; }
-    else sr = wave_radix_select<VPT>(key, nv, (uint32_t)a.k, hist);
-    const Placement pl = place<WAVE, VPT>(key, nv, sr, scratch);
-
-    uint32_t* idx = a.idx + seg * a.k;
-    R* val = (R*)a.val + seg * a.k;
-    uint32_t pos = pl.pos, ties = 0;
-    float eo[VPT];
+    // ---- payload entries into LDS, in index order; the epilogue's rows out
 #pragma unroll
-    for (int i = 0; i < VPT; ++i) {
-      bool kept = false;
-      if (i < nv) {
-        const bool tie = key[i] == sr.T;
-        kept = key[i] > sr.T || (tie && ties < pl.tie_keep);
-        ties += tie ? 1u : 0u;
-        if (kept) {
-          const R w = Elem<InT>::down(v[i]);
-          if (pos < a.k) { idx[pos] = (uint32_t)(c0 + i); val[pos] = w; }
-          else raise_error(KERR_INTERNAL);
-          ++pos;
-          if constexpr (SEL == SEL_AQSGD) mr[i] = Elem<InT>::down(Elem<InT>::up(mr[i]) + Elem<InT>::up(w));
+    for (int p = 0; p < NP; ++p) {
+      const uint32_t o = (uint32_t)p * ROW_PIECE + lane * 4u;
+      uint32_t pos = ex[p];
+      float eo[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t on = (km[p] >> i) & 1u;
+        const R w = Elem<InT>::down(v[p][i]);
+        const uint32_t slot = on ? pos : ROW_PIECE * NP + lane;
+        if constexpr (sizeof(R) == 2) {
+          st.w[slot] = (o + (uint32_t)i) | ((uint32_t)w << 16);
+        } else {
+          st.w[slot] = __float_as_uint(w);
+          st.i[slot] = (uint16_t)(o + (uint32_t)i);
+        }
+        pos += on;
+        if constexpr (SEL == SEL_EF) eo[i] = v[p][i] - (on ? Elem<InT>::up(w) : 0.0f);
+        if constexpr (SEL == SEL_AQSGD) {
+          const R upd = Elem<InT>::down(Elem<InT>::up(mr[p][i]) + Elem<InT>::up(w));
+          mr[p][i] = on ? upd : mr[p][i];
         }
       }
-      if constexpr (SEL == SEL_EF) eo[i] = v[i] - (kept ? through<InT>(v[i]) : 0.0f);
+      if constexpr (SEL == SEL_EF) {
+        if (vec) {
+          if (o < L) store_run<float, 4, true>(es + o, eo);
+        } else if (o + 4u <= L) {
+          store_piece_any<float>(es + o, eo);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (o + (uint32_t)i < L) es[o + i] = eo[i];
+        }
+      }
+      if constexpr (SEL == SEL_AQSGD) {
+        if (k > 0u) {
+          if (o + 4u <= L) {
+            store_piece_any<R>(mrow + o, mr[p]);
+          } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (o + (uint32_t)i < L) mrow[o + i] = mr[p][i];
+          }
+        }
+      }
     }
-    if constexpr (SEL == SEL_EF) {
-      if (nv > 0) store_run_partial<float, VPT, true>(a.e + seg * a.L + c0, nv, eo);
+    // ---- the payload out (a wavefront's LDS accesses complete in program order)
+    __builtin_amdgcn_wave_barrier();
+    uint32_t* const idx = a.idx + seg * a.k;
+    R* const val = (R*)a.val + seg * a.k;
+    for (uint32_t j = lane; j < k; j += WAVE) {
+      const uint32_t w = st.w[j];
+      if constexpr (sizeof(R) == 2) {
+        idx[j] = w & 0xFFFFu;
+        val[j] = (R)(w >> 16);
+      } else {
+        idx[j] = st.i[j];
+        val[j] = __uint_as_float(w);
+      }
     }
-    if constexpr (SEL == SEL_AQSGD) {
-      if (nv > 0 && a.k > 0) store_run_partial<R, VPT, false>((R*)a.m + mrow + c0, nv, mr);
-    }
-    if (a.blk && threadIdx.x == 0) {
-      // a wavefront segment is shorter than one block
+    __builtin_amdgcn_wave_barrier();
+    if (a.blk && lane == 0) {
+      // a row is shorter than one block
       uint32_t* bt = a.blk + seg * (n_blocks(a.L) + 1);
       bt[0] = 0;
-      bt[n_blocks(a.L)] = (uint32_t)a.k;
+      bt[n_blocks(a.L)] = k;
     }
   }
 }
@@ -1301,12 +1472,12 @@ static_assert(ROW_MAX <= BLOCK_LEN, "a wavefront segment fits in one block of th
 template <typename InT, int SEL>
 const void* row_ptr(int vpt) {
   switch (vpt) {
-    case 4: return (const void*)k_topk_row<InT, SEL, 4>;
-    case 8: return (const void*)k_topk_row<InT, SEL, 8>;
-    case 12: return (const void*)k_topk_row<InT, SEL, 12>;
-    case 16: return (const void*)k_topk_row<InT, SEL, 16>;
-    case 24: return (const void*)k_topk_row<InT, SEL, 24>;
-    case 32: return (const void*)k_topk_row<InT, SEL, 32>;
+    case 4: return (const void*)k_topk_row<InT, SEL, 1>;
+    case 8: return (const void*)k_topk_row<InT, SEL, 2>;
+    case 12: return (const void*)k_topk_row<InT, SEL, 3>;
+    case 16: return (const void*)k_topk_row<InT, SEL, 4>;
+    case 24: return (const void*)k_topk_row<InT, SEL, 6>;
+    case 32: return (const void*)k_topk_row<InT, SEL, 8>;
   }
   return nullptr;
 }
@@ -1439,7 +1610,9 @@ SegPlan plan_topk(int sel, int dt, uint64_t n_seg, uint64_t L) {
     p.P = 1;
     const uint64_t cap = (uint64_t)occupancy(pick(sel, dt, true, p.vpt), p.nt) * cus;
     p.capacity = cap;
-    p.n_groups = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(n_seg, cap));
+    // a workgroup per row (rows need no other workgroup, so more than the
+    // device holds at once are fine)
+    p.n_groups = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(n_seg, 1u << 20));
     p.grid = p.n_groups;
     p.ws_words = 0;
     return p;

@@ -188,6 +188,22 @@ __device__ __forceinline__ void load_piece(const Raw* p, Raw (&out)[4]) {
   }
 }
 
+// the same for a piece aligned to its elements only (the hardware takes
+// unaligned vector accesses; a piece across a line costs a second request)
+template <typename Raw>
+__device__ __forceinline__ void load_piece_any(const Raw* p, Raw (&out)[4]) {
+  struct __attribute__((packed, aligned(sizeof(Raw)))) Piece { Raw v[4]; };
+  const Piece w = *reinterpret_cast<const Piece*>(p);
+  __builtin_memcpy(out, &w, sizeof(w));
+}
+template <typename Raw>
+__device__ __forceinline__ void store_piece_any(Raw* p, const Raw (&in)[4]) {
+  struct __attribute__((packed, aligned(sizeof(Raw)))) Piece { Raw v[4]; };
+  Piece w;
+  __builtin_memcpy(&w, in, sizeof(w));
+  *reinterpret_cast<Piece*>(p) = w;
+}
+
 // Load a run that may be cut short at `n` valid elements (n <= N); elements
 // past n are left as `fill`.
 template <typename R, int N, bool STREAM = false>
@@ -281,6 +297,27 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
 
 __device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(x), WAVE - 1);
+}
+
+// sum over the wavefront, of floats (in the same lane pattern) or of bits
+__device__ __forceinline__ float wave_fsum(float x) {
+  auto add = [](float a, uint32_t b) { return a + __uint_as_float(b); };
+  x = add(x, dpp_u32<DPP_ROW_SHR1, 0xF>(0u, __float_as_uint(x)));
+  x = add(x, dpp_u32<DPP_ROW_SHR2, 0xF>(0u, __float_as_uint(x)));
+  x = add(x, dpp_u32<DPP_ROW_SHR4, 0xF>(0u, __float_as_uint(x)));
+  x = add(x, dpp_u32<DPP_ROW_SHR8, 0xF>(0u, __float_as_uint(x)));
+  x = add(x, dpp_u32<DPP_ROW_BCAST15, 0xA>(0u, __float_as_uint(x)));
+  x = add(x, dpp_u32<DPP_ROW_BCAST31, 0xC>(0u, __float_as_uint(x)));
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), WAVE - 1));
+}
+__device__ __forceinline__ uint32_t wave_or(uint32_t x) {
+  x |= dpp_u32<DPP_ROW_SHR1, 0xF>(0u, x);
+  x |= dpp_u32<DPP_ROW_SHR2, 0xF>(0u, x);
+  x |= dpp_u32<DPP_ROW_SHR4, 0xF>(0u, x);
+  x |= dpp_u32<DPP_ROW_SHR8, 0xF>(0u, x);
+  x |= dpp_u32<DPP_ROW_BCAST15, 0xA>(0u, x);
+  x |= dpp_u32<DPP_ROW_BCAST31, 0xC>(0u, x);
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, WAVE - 1);
 }
 
 // running min / max in the same lane pattern; lane 63 ends with the result

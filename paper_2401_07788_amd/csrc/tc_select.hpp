@@ -5,9 +5,9 @@
 // key T and the tie quota r = k - #(key > T) define the kept set:
 //   key > T, or key == T and the entry is among the r lowest-index ties.
 //
-// Shared pieces: bin search over histograms in LDS, and the one-wavefront strategy for short segments (a token row):
-// a radix select over 8-bit digits with a wavefront-private histogram.  The
-// several-workgroup strategy is in tc_group.hpp.
+// Shared pieces: bin search over histograms in LDS, and the one-wavefront
+// strategy for short segments (a token row).  The several-workgroup strategy is
+// in tc_group.hpp.
 #pragma once
 
 #include "tc_device.hpp"
@@ -97,171 +97,172 @@ __device__ __forceinline__ void zero_lds(uint32_t* h, int n) {
   for (int b = (int)threadIdx.x; b < n; b += NT) h[b] = 0u;
 }
 
-// Exact threshold for a segment held entirely by one wavefront (NT == 64):
-// radix select over 8-bit digits of the key from bit 23 down, then its last
-// 7 bits, with 256-bin histograms in LDS private to the wavefront (`hist`,
-// 16-byte aligned, RADIX_CP * RADIX_HS words); each digit is found with one
-// wavefront scan (lane l owns bins 4l..4l+3).
-//  - The first digit is the exponent.  With at most 15 keys per lane it is
-//    counted in registers first: a 4-bit counter per lane for each of the
-//    eight digits at and below the segment's largest, summed over the
-//    wavefront in four words.  Only when T's digit lies further down does
-//    the histogram pass run.
-//  - In that pass the exponent takes few values, so the lanes count in
-//    RADIX_CP copies (lane mod RADIX_CP), RADIX_HS words apart: an odd
-//    number of 4-word bank groups, so that one bin's copies sit in distinct
-//    LDS banks.
-//  - Once the chosen bin must give up only its largest key (one more
-//    needed) or all of its keys, the rest of T is that largest or smallest
-//    key, found by one wavefront reduction instead of the remaining passes
-//    (after two digits a row's bin holds about one key).
-constexpr int RADIX_CP = 4;
-constexpr int RADIX_HS = 260;
-template <int VPT>
-__device__ __forceinline__ SelResult wave_radix_select(const uint32_t (&key)[VPT], int nv, uint32_t k,
-                                                       uint32_t* hist) {
-  const uint32_t lane = (uint32_t)lane_id();
-  uint32_t prefix = 0u, need = k, pbits = 0u;
-  // T from the keys under `prefix` (pbits bits): their largest (one copy
-  // kept) or their smallest (all copies kept)
-  auto settle = [&](bool top) {
-    const uint32_t sh = 31u - pbits;
-    uint32_t best = top ? 0u : 0xFFFFFFFFu;
-#pragma unroll
-    for (int i = 0; i < VPT; ++i)
-      if (i < nv && (key[i] >> sh) == prefix) best = top ? max(best, key[i]) : min(best, key[i]);
-    SelResult res;
-    res.T = top ? wave_uminmax<true>(best) : wave_uminmax<false>(best);
-    uint32_t eq = 0u;
-    if (!top) {
-#pragma unroll
-      for (int i = 0; i < VPT; ++i) eq += (i < nv && key[i] == res.T) ? 1u : 0u;
-    }
-    res.r = top ? 1u : wave_sum(eq);
-    res.gt_before = 0u;
-    res.eq_before = 0u;
-    return res;
-  };
-  int first = 0;   // digit passes already done
-  if constexpr (VPT <= 15) {
-    uint32_t dm = 0u;
-#pragma unroll
-    for (int i = 0; i < VPT; ++i)
-      if (i < nv) dm = max(dm, key[i] >> 23);
-    dm = wave_uminmax<true>(dm);
-    uint32_t w = 0u;   // nibble o: keys of digit dm - o
-#pragma unroll
-    for (int i = 0; i < VPT; ++i) {
-      const uint32_t off = dm - (key[i] >> 23);
-      w += (i < nv && off < 8u) ? (1u << (off << 2)) : 0u;
-    }
-    // widened to 16-bit fields before the sums: words hold digits (0, 4),
-    // (2, 6), (1, 5), (3, 7)
-    const uint32_t ev = w & 0x0F0F0F0Fu, od = (w >> 4) & 0x0F0F0F0Fu;
-    const uint32_t s04 = wave_sum(ev & 0x00FF00FFu), s26 = wave_sum((ev >> 8) & 0x00FF00FFu);
-    const uint32_t s15 = wave_sum(od & 0x00FF00FFu), s37 = wave_sum((od >> 8) & 0x00FF00FFu);
-    const uint32_t c8[8] = {s04 & 0xFFFFu, s15 & 0xFFFFu, s26 & 0xFFFFu, s37 & 0xFFFFu,
-                            s04 >> 16,     s15 >> 16,     s26 >> 16,     s37 >> 16};
-    uint32_t acc = 0u, cnt = 0u;
-#pragma unroll
-    for (int o = 0; o < 8; ++o) {
-      if (first == 0 && acc < need && need <= acc + c8[o]) {
-        first = 1;
-        prefix = dm - (uint32_t)o;
-        need -= acc;
-        cnt = c8[o];
-      }
-      acc += c8[o];
-    }
-    if (first) {
-      pbits = 8u;
-      if (need == 1u || need == cnt) return settle(need == 1u);
-    }
+// The threshold by counting: C(t) = #(key >= t) over the segment for a few
+// trial keys t, which narrow a bracket lo < hi with C(lo) > k > C(hi) (or lo
+// = 0, hi = 2^31).  Every lane holds the same values, on the scalar unit but
+// for the guess itself.  Trials are guessed from the counts: the first as if
+// magnitudes were exponentially distributed around their mean mu, then by
+// interpolation of log C between the ends, in value where the bracket spans
+// octaves (a heavy tail or a mass at zero bends log C there), in key
+// otherwise.  From the eighth trial on each halves the bracket in key, which
+// bounds the search at 39 trials for any input.  Keys are multiples of 2^tz,
+// and so are lo and hi: 16-bit inputs need no search below their last bit.
+// Only which t is tried depends on floating point; the counts decide.
+struct CountSearch {
+  uint32_t lo = 0u, hi = 0x80000000u;   // trial keys: C(lo) = cl, C(hi) = ch
+  uint32_t cl, ch = 0u, n = 0u;
+  uint32_t k, tz;
+  float mu, lk, la, lb = -1.0f;         // log2 of k, cl, ch (of 1/2 for ch = 0)
+  __device__ __forceinline__ CountSearch(uint32_t L, uint32_t k_, uint32_t tz_, float mu_, float lk_, float lL)
+      : cl(L), k(k_), tz(tz_), mu(mu_), lk(lk_), la(lL) {}
+  __device__ __forceinline__ bool closed() const { return hi - lo <= (1u << tz); }   // T = lo, k - ch ties kept
+  // a key strictly inside the bracket, a multiple of 2^tz, near t
+  __device__ __forceinline__ uint32_t inside(uint32_t t) const {
+    const uint32_t g = 1u << tz;
+    t = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
+    t = min(max(t, lo), hi - 1u);
+    t = lo + max(g, ((t - lo) >> tz) << tz);
+    return min(t, hi - g);
   }
-#pragma unroll
-  for (int pass = 0; pass < 4; ++pass) {
-    if (pass < first) continue;
-    const uint32_t width = (pass < 3) ? 8u : 7u;
-    const uint32_t shift = 31u - pbits - width;
-    constexpr int CP = RADIX_CP;
-#pragma unroll
-    for (int c = 0; c < (pass == 0 ? CP : 1); ++c)
-      reinterpret_cast<u32x4*>(hist)[c * (RADIX_HS / 4) + lane] = u32x4{0u, 0u, 0u, 0u};
-    __syncthreads();
-    const uint32_t base = (pass == 0) ? (lane % CP) * (uint32_t)RADIX_HS : 0u;
-#pragma unroll
-    for (int i = 0; i < VPT; ++i)
-      if (i < nv && (key[i] >> (shift + width)) == prefix)
-        atomicAdd(&hist[base + ((key[i] >> shift) & ((1u << width) - 1u))], 1u);
-    __syncthreads();
-    u32x4 h = reinterpret_cast<const u32x4*>(hist)[lane];
-    if (pass == 0) {
-#pragma unroll
-      for (int c = 1; c < CP; ++c) {
-        const u32x4 hc = reinterpret_cast<const u32x4*>(hist)[c * (RADIX_HS / 4) + lane];
-        h = h + hc;
-      }
-    }
-    const uint32_t sum = h[0] + h[1] + h[2] + h[3];
-    const uint32_t incl = wave_incl_scan(sum);
-    uint32_t acc = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1) - incl;   // bins of higher lanes
-    uint32_t d = 0u, cnt = 0u;
-    const bool here = acc < need && need <= acc + sum;
-    if (here) {
-#pragma unroll
-      for (int c = 3; c >= 0; --c) {
-        if (acc + h[c] >= need) { d = 4u * lane + (uint32_t)c; cnt = h[c]; break; }
-        acc += h[c];
-      }
-    }
-    const int src = __builtin_ctzll(__ballot(here));
-    d = (uint32_t)__builtin_amdgcn_readlane((int)d, src);
-    acc = (uint32_t)__builtin_amdgcn_readlane((int)acc, src);
-    cnt = (uint32_t)__builtin_amdgcn_readlane((int)cnt, src);
-    prefix = (prefix << width) | d;
-    need -= acc;
-    pbits += width;
-    __syncthreads();
-    if (pass < 3 && (need == 1u || need == cnt)) return settle(need == 1u);
+  // lg = 0.95 ln(L / k + 0.15)
+  __device__ __forceinline__ uint32_t first(float lg) const { return inside(__float_as_uint(mu * lg)); }
+  __device__ __forceinline__ void update(uint32_t t, uint32_t c) {
+    const float l = c ? __builtin_amdgcn_logf((float)c) : -1.0f;
+    // (selects, one per member: branches would leave the object in memory)
+    const bool low = c > k;
+    lo = low ? t : lo;
+    cl = low ? c : cl;
+    la = low ? l : la;
+    hi = low ? hi : t;
+    ch = low ? ch : c;
+    lb = low ? lb : l;
+    ++n;
   }
-  SelResult res;
-  res.T = prefix;
-  res.r = need;
-  res.gt_before = 0u;
-  res.eq_before = 0u;
-  return res;
-}
-
-// Per-thread output placement after selection.  Entries of a thread are
-// contiguous and in index order, threads in index order, workgroups of a
-// segment in index order.
-struct Placement {
-  uint32_t pos;        // payload slot of this thread's first kept entry
-  uint32_t tie_keep;   // how many of this thread's ties are kept
-  uint32_t wg_first;   // payload slot of the workgroup's first kept entry
-  uint32_t wg_count;   // entries the workgroup keeps
+  __device__ __forceinline__ uint32_t next() const {
+    constexpr float LN2 = 0.6931472f;
+    if (n >= 8u) return inside(lo + ((hi - lo) >> 1));
+    if (hi == 0x80000000u)                // no upper end yet: out by the mean, doubling
+      return inside(__float_as_uint(__uint_as_float(lo) + mu * LN2 * (la - lk) * (float)(1u << (n - 1u))));
+    if (lo == 0u) {                       // no lower end yet: down once, then "not zero"
+      if (n >= 2u) return inside(1u);
+      const float h = __uint_as_float(hi);
+      return inside(__float_as_uint(fmaxf(h - 1.1f * mu * LN2 * (lk - lb), 0.25f * h)));
+    }
+    const float f = (la - lk) * __builtin_amdgcn_rcpf(la - lb);
+    if (hi - lo > (1u << 24) && (n & 1u) == 0u) {
+      const float l = __uint_as_float(lo);
+      return inside(__float_as_uint(l + (__uint_as_float(hi) - l) * f));
+    }
+    return inside(lo + (uint32_t)((float)(hi - lo) * f));
+  }
 };
 
-template <int NT, int VPT>
-__device__ __forceinline__ Placement place(const uint32_t (&key)[VPT], int nv, const SelResult& s,
-                                           uint32_t* scratch) {
-  uint32_t gt = 0, eq = 0;
+// Exact threshold for a segment held by one wavefront, V keys per lane (keys
+// past the segment's L are 0 and come after it): the k-th largest key T, or
+// any T' with exactly k keys at or above it.  Four rows share a SIMD, so what
+// counts is instructions issued: a trial key costs two per key for one bit of
+// T, a histogram five for nine bits.  So the first guess places a window of
+// two octaves on either side of it, 512 bins of 1/128 octave (one to four keys
+// of a row each around T), counted with LDS atomics (keys below the window in
+// a word per lane, so that they do not meet in one); T's bin then gives up
+// its keys from the nearer end, a wavefront reduction each.  A window that
+// missed T, or a bin with many keys, leaves the rest to trial keys.
+// 1 <= k <= L; tz as above, at most RW_SHIFT.
+constexpr uint32_t RW_BINS = 512, RW_SHIFT = 16;            // 2^25: four octaves
+constexpr uint32_t RW_WORDS = RW_BINS + WAVE;               // LDS words (16-byte aligned)
+struct RowLogs {
+  float lk, lL, lg;   // log2 k, log2 L, the first guess's factor
+};
+template <int V>
+__device__ __forceinline__ uint32_t wave_select_key(const uint32_t (&key)[V], uint32_t L, uint32_t k, uint32_t tz,
+                                                    float mu, const RowLogs& lg, uint32_t* hist) {
+  CountSearch s(L, k, tz, mu, lg.lk, lg.lL);
+  const uint32_t t0 = s.first(lg.lg);
+  const uint32_t lane = (uint32_t)lane_id();
+  {
+    const uint32_t base = (t0 - min(t0, 2u << 23)) & ~((1u << RW_SHIFT) - 1u);
+    uint32_t* const bins = hist + WAVE;
+    reinterpret_cast<u32x4*>(bins)[lane] = u32x4{0u, 0u, 0u, 0u};
+    reinterpret_cast<u32x4*>(bins)[lane + WAVE] = u32x4{0u, 0u, 0u, 0u};
+    __builtin_amdgcn_wave_barrier();
+    const int below = -1 - (int)lane;
 #pragma unroll
-  for (int v = 0; v < VPT; ++v) {
-    if (v < nv) { gt += key[v] > s.T; eq += key[v] == s.T; }
+    for (int i = 0; i < V; ++i) {
+      const int b = (int)(key[i] - base) >> RW_SHIFT;
+      atomicAdd(&bins[min(max(b, below), (int)RW_BINS - 1)], 1u);
+    }
+    __builtin_amdgcn_wave_barrier();
+    const u32x4 h0 = reinterpret_cast<const u32x4*>(bins)[2 * lane], h1 = reinterpret_cast<const u32x4*>(bins)[2 * lane + 1];
+    const uint32_t h[8] = {h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w};
+    const uint32_t sum = ((h[0] + h[1]) + (h[2] + h[3])) + ((h[4] + h[5]) + (h[6] + h[7]));
+    const uint32_t incl = wave_incl_scan(sum);
+    uint32_t acc = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1) - incl;   // keys in bins of higher lanes
+    const uint64_t here = __ballot(acc < k && k <= acc + sum);
+    if (here) {
+      const int src = __builtin_ctzll(here);
+      uint32_t above = acc, bin = 0u, cnt = 0u;
+#pragma unroll
+      for (int c = 7; c >= 0; --c) {
+        const bool on = acc < k;          // the last such bin, from the top, is T's
+        above = on ? acc : above;
+        bin = on ? (uint32_t)c : bin;
+        cnt = on ? h[c] : cnt;
+        acc += h[c];
+      }
+      bin = 8u * (uint32_t)src + (uint32_t)__builtin_amdgcn_readlane((int)bin, src);
+      above = (uint32_t)__builtin_amdgcn_readlane((int)above, src);
+      cnt = (uint32_t)__builtin_amdgcn_readlane((int)cnt, src);
+      const uint32_t lo = base + (bin << RW_SHIFT);
+      // (the last bin has no upper end; one that starts at key 0 counts the
+      // keys past the segment's end)
+      if (bin < RW_BINS - 1u && lo > 0u) {
+        if (above + cnt == k) return lo;
+        s.update(lo, above + cnt);
+        s.update(lo + (1u << RW_SHIFT), above);
+      }
+    }
   }
-  // both counts stay below 2^16 per workgroup (NT * VPT <= 32768)
-  uint32_t tot;
-  const uint32_t ex = block_excl_scan<NT>(gt | (eq << 16), scratch, tot);
-  const uint32_t gt_ex = ex & 0xFFFFu, eq_ex = ex >> 16, eq_wg = tot >> 16;
-  const uint32_t quota_wg = min(sat_sub(s.r, s.eq_before), eq_wg);
-  const uint32_t mine = min(sat_sub(quota_wg, eq_ex), eq);
-  Placement p;
-  p.wg_first = s.gt_before + min(s.eq_before, s.r);
-  p.wg_count = (tot & 0xFFFFu) + quota_wg;
-  p.pos = p.wg_first + gt_ex + min(eq_ex, quota_wg);
-  p.tie_keep = mine;
-  return p;
+  for (;;) {
+    for (;;) {
+      if (s.closed()) return s.lo;
+      const uint32_t near = (s.n < 5u) ? 3u : 6u;
+      const uint32_t up = k - s.ch, dn = (s.lo > 0u) ? s.cl - k : 0xFFFFFFFFu;
+      if (min(up, dn) > near) break;
+      uint32_t T, m = 0;
+      if (up <= dn) {
+        // the largest key below hi: differences wrap for those below
+        uint32_t best = 0u;
+#pragma unroll
+        for (int i = 0; i < V; ++i) best = max(best, key[i] - s.hi);
+        T = wave_uminmax<true>(best) + s.hi;
+        if (up == 1u) return T;
+      } else {
+        // the smallest key from lo on: differences wrap for those below
+        uint32_t best = 0xFFFFFFFFu;
+#pragma unroll
+        for (int i = 0; i < V; ++i) best = min(best, key[i] - s.lo);
+        T = wave_uminmax<false>(best) + s.lo;
+      }
+#pragma unroll
+      for (int i = 0; i < V; ++i) m += (uint32_t)__popcll(__ballot(key[i] == T));
+      const bool top = up <= dn;
+      if (m > dn || (top && m >= up)) return T;
+      if (!top && m == dn) return T + 1u;
+      s.hi = top ? T : s.hi;
+      s.ch += top ? m : 0u;
+      s.lo = top ? s.lo : T + (1u << tz);
+      s.cl -= top ? 0u : m;
+    }
+    // a trial key: a lane counts its own keys and the lanes' counts are added
+    // once (the scalar unit would take a population count and an addition per key)
+    const uint32_t t = s.n ? s.next() : t0;
+    uint32_t under = 0;      // a bit per key below t
+#pragma unroll
+    for (int i = 0; i < V; ++i) under = __builtin_amdgcn_alignbit(under, key[i] - t, 31);
+    const uint32_t c = (uint32_t)WAVE * V - wave_sum((uint32_t)__builtin_popcount(under));
+    if (c == k) return t;
+    s.update(t, c);
+  }
 }
 
 }  // namespace tc
