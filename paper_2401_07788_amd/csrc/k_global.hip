@@ -156,14 +156,28 @@ __device__ __forceinline__ void load_tile_values(const GlobalArgs& a, uint64_t t
   }
 }
 
-// One thread's 16 elements of a whole tile as loaded (16-byte accesses),
-// fetched one tile ahead in the band and emit passes, so that the next
-// tile's loads are in flight while this one is worked on.
+// Band and emit: a wavefront takes 1024 consecutive elements of the tile in
+// four pieces of 256; piece q of lane l is the wavefront's elements
+// q * 256 + 4 l .. + 3, so that every wavefront access covers whole lines
+// (runs of 16 elements per thread cover each line over four accesses, and
+// their LDS copies meet in a quarter of the banks).  2^27 bfloat16 with EF,
+// TopK 10 % at 4 bits: band 172 -> 150 us (5.4 TB/s), emit 345 -> 315 (4.4
+// TB/s read and written), with emit's loads and stores non-temporal (660 us a
+// step without its loads' hint, 640 with; on band's loads it gains nothing).
+constexpr uint32_t G_WAVE = (uint32_t)G_TILE / (G_NT / WAVE);   // elements per wavefront
+constexpr int G_NP = G_VPT / 4;                                 // pieces per lane
+static_assert(G_WAVE == (uint32_t)G_NP * 4u * WAVE, "whole pieces");
+__device__ __forceinline__ uint32_t piece_at(int q) {
+  return (threadIdx.x / WAVE) * G_WAVE + (uint32_t)q * (4u * WAVE) + (uint32_t)lane_id() * 4u;
+}
+
+// One lane's pieces of a whole tile as loaded, fetched one tile ahead in the
+// band and emit passes, so that the next tile's loads are in flight while
+// this one is worked on.
 template <typename InT, bool EF>
 struct TileRaw {
-  static constexpr int XW = G_VPT * (int)sizeof(typename Elem<InT>::raw) / 16;
-  u32x4 x[XW];
-  u32x4 e[EF ? G_VPT / 4 : 1];
+  typename Elem<InT>::raw x[G_NP][4];
+  float e[EF ? G_NP : 1][4];
 };
 // whole 16-byte runs: both arrays 16-byte aligned
 __device__ __forceinline__ bool tiles_prefetchable(const GlobalArgs& a) {
@@ -173,34 +187,53 @@ __device__ __forceinline__ bool tiles_prefetchable(const GlobalArgs& a) {
 __device__ __forceinline__ bool tile_whole(const GlobalArgs& a, uint64_t tile) {
   return tile < a.n_tiles && (tile + 1) * G_TILE <= a.L;
 }
-template <typename InT, bool EF>
+template <typename InT, bool EF, bool STREAM>
 __device__ __forceinline__ void tile_fetch(const GlobalArgs& a, uint64_t tile, TileRaw<InT, EF>& r) {
   using R = typename Elem<InT>::raw;
-  const uint64_t t0 = tile * G_TILE + (uint64_t)threadIdx.x * G_VPT;
-  const u32x4* px = reinterpret_cast<const u32x4*>((const R*)a.x + t0);
+  const uint64_t t0 = tile * G_TILE;
 #pragma unroll
-  for (int i = 0; i < TileRaw<InT, EF>::XW; ++i) r.x[i] = px[i];
-  if constexpr (EF) {
-    const u32x4* pe = reinterpret_cast<const u32x4*>(a.e + t0);
-#pragma unroll
-    for (int i = 0; i < G_VPT / 4; ++i) r.e[i] = pe[i];
+  for (int q = 0; q < G_NP; ++q) {
+    load_piece<R, STREAM>((const R*)a.x + t0 + piece_at(q), r.x[q]);
+    if constexpr (EF) load_piece<float, STREAM>(a.e + t0 + piece_at(q), r.e[q]);
   }
 }
 template <typename InT, bool EF>
 __device__ __forceinline__ void tile_values(const TileRaw<InT, EF>& r, float (&v)[G_VPT]) {
+#pragma unroll
+  for (int q = 0; q < G_NP; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float x = Elem<InT>::up(r.x[q][i]);
+      if constexpr (EF) x = x + r.e[q][i];
+      v[4 * q + i] = x;
+    }
+}
+// the same for a tile cut by the segment's end, or unaligned arrays: element
+// by element (+0 past the end)
+template <typename InT, bool EF>
+__device__ __forceinline__ void tile_values_any(const GlobalArgs& a, uint64_t tile, float (&v)[G_VPT]) {
   using R = typename Elem<InT>::raw;
 #pragma unroll
-  for (int i = 0; i < G_VPT; ++i) {
-    float x;
-    if constexpr (sizeof(R) == 4) {
-      x = __uint_as_float(r.x[i / 4][i % 4]);
-    } else {
-      const uint32_t w = r.x[i / 8][(i % 8) / 2];
-      x = Elem<InT>::up((R)((i & 1) ? (w >> 16) : (w & 0xFFFFu)));
+  for (int q = 0; q < G_NP; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint64_t at = tile * G_TILE + piece_at(q) + (uint32_t)i;
+      float x = 0.0f;
+      if (at < a.L) {
+        x = Elem<InT>::up(((const R*)a.x)[at]);
+        if constexpr (EF) x = x + a.e[at];
+      }
+      v[4 * q + i] = x;
     }
-    if constexpr (EF) x = x + __uint_as_float(r.e[i / 4][i % 4]);
-    v[i] = x;
-  }
+}
+// bit 4 q + i: element i of piece q lies in the segment
+__device__ __forceinline__ uint32_t tile_valid(const GlobalArgs& a, uint64_t tile) {
+  if (tile_whole(a, tile)) return 0xFFFFu;
+  const uint32_t n = (uint32_t)(a.L - tile * G_TILE);   // elements in the tile
+  uint32_t m = 0;
+#pragma unroll
+  for (int q = 0; q < G_NP; ++q) m |= ((1u << min(4u, sat_sub(n, piece_at(q)))) - 1u) << (4 * q);
+  return m;
 }
 
 __device__ __forceinline__ void zero_lds_bins(uint32_t* h, int nb) {
@@ -343,17 +376,16 @@ __global__ __launch_bounds__(G_NT) void k_g_band(GlobalArgs a) {
   const bool pf = tiles_prefetchable(a);
   TileRaw<InT, EF> nxt;
   bool have = pf && tile_whole(a, blockIdx.x);
-  if (have) tile_fetch<InT, EF>(a, blockIdx.x, nxt);
+  if (have) tile_fetch<InT, EF, false>(a, blockIdx.x, nxt);
   for (uint64_t tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
-    const uint64_t t0 = tile * G_TILE + (uint64_t)threadIdx.x * G_VPT;
-    const int nv = (int)min((uint64_t)G_VPT, sat_sub(a.L, t0));
     float v[G_VPT];
     if (have) tile_values<InT, EF>(nxt, v);
-    else load_tile_values<InT, EF>(a, t0, nv, v);
+    else tile_values_any<InT, EF>(a, tile, v);
     have = pf && tile_whole(a, tile + gridDim.x);
-    if (have) tile_fetch<InT, EF>(a, tile + gridDim.x, nxt);
+    if (have) tile_fetch<InT, EF, false>(a, tile + gridDim.x, nxt);
     // above the band / inside it, as bit masks (bit i: element i); digits
-    // are 12-bit, so the sign bit of a difference compares them
+    // are 12-bit, so the sign bit of a difference compares them.  (Values
+    // past the segment's end are +0: never above the band.)
     uint32_t am = 0, bm = 0;
 #pragma unroll
     for (int i = 0; i < G_VPT; ++i) {
@@ -364,7 +396,7 @@ __global__ __launch_bounds__(G_NT) void k_g_band(GlobalArgs a) {
       amin = fminf(amin, up ? v[i] : __builtin_inff());
       amax = fmaxf(amax, up ? v[i] : -__builtin_inff());
     }
-    const uint32_t valid = (nv >= G_VPT) ? 0xFFFFu : ((1u << max(nv, 0)) - 1u);
+    const uint32_t valid = tile_valid(a, tile);
     bm &= valid;
     const uint32_t above = (uint32_t)__builtin_popcount(am & valid), inb = (uint32_t)__builtin_popcount(bm);
     uint32_t tot;
@@ -385,11 +417,12 @@ __global__ __launch_bounds__(G_NT) void k_g_band(GlobalArgs a) {
         u32x4 w;
 #pragma unroll
         for (int i = 0; i < 4; ++i) w[i] = __float_as_uint(v[4 * q + i]);
-        *reinterpret_cast<u32x4*>(&s_vals[threadIdx.x * G_VPT + 4 * q]) = w;
+        *reinterpret_cast<u32x4*>(&s_vals[piece_at(q)]) = w;
       }
       off += nbuf;
       for (uint32_t m = bm; m; m &= m - 1u) {
-        const uint32_t bits = s_vals[threadIdx.x * G_VPT + (uint32_t)__builtin_ctz(m)];
+        const uint32_t i = (uint32_t)__builtin_ctz(m);
+        const uint32_t bits = s_vals[piece_at((int)(i >> 2)) + (i & 3u)];
         s_cand[off++] = bits;
         if (count_digits) atomicAdd(&s_bd[((bits & 0x7FFFFFFFu) >> 19) - blo], 1u);
       }
@@ -810,22 +843,43 @@ __device__ __forceinline__ void write_codes(uint32_t* codes, uint64_t wpg, uint6
   }
 }
 
+// exclusive prefix sums over a wavefront's elements, in order, of one count
+// per piece (0 to 4 per lane): two pieces share a word
+__device__ __forceinline__ uint32_t wave_piece_scan(const uint32_t (&n)[G_NP], uint32_t (&ex)[G_NP]) {
+  static_assert(G_NP % 2 == 0, "pairs of pieces");
+  uint32_t base = 0;
+#pragma unroll
+  for (int q = 0; q < G_NP; q += 2) {
+    const uint32_t w = n[q] | (n[q + 1] << 16);
+    const uint32_t incl = wave_incl_scan(w);
+    const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
+    const uint32_t x = incl - w;
+    ex[q] = base + (x & 0xFFFFu);
+    base += tot & 0xFFFFu;
+    ex[q + 1] = base + (x >> 16);
+    base += tot >> 16;
+  }
+  return base;
+}
+
 // Q = 0: TopK values in the input dtype; Q = b: the kept list quantized.
-// Per tile: (1) every thread marks its kept entries (bit masks), the tile's
-// values go to LDS and the kept entries' offsets are compacted there; (2)
-// the kept entries alone (about one in ten) are encoded, written to the
-// payload, and their residual replaces the value in LDS; (3) the dense
-// residual leaves from LDS.  Per-element work is thus only the two key
-// comparisons; the encoding runs on the compacted list.
+// Per tile: (1) every lane marks its kept entries (bit masks), the tile's
+// values go to LDS and the kept entries' offsets are compacted there, a list
+// per wavefront; (2) the kept entries alone (about one in ten) are encoded,
+// written to the payload, and their residual replaces the value in LDS; (3)
+// the dense residual leaves from LDS.  Per-element work is thus only the two
+// key comparisons; the encoding runs on the compacted list.  The wavefronts
+// meet once for their counts and once for the codes' words.
 template <typename InT, bool EF, uint32_t Q>
 __global__ __launch_bounds__(G_NT) void k_g_emit(GlobalArgs a) {
   using R = typename Elem<InT>::raw;
   constexpr bool QK = Q != 0;
   constexpr bool CODES = QK && Q != 32;   // b-bit codes, packed from LDS
   __shared__ __attribute__((aligned(16))) uint32_t s_v[G_TILE];   // the tile's values (binary32 bits)
-  __shared__ uint16_t s_off[G_TILE];        // kept entries' offsets in the tile, in order
+  __shared__ uint16_t s_off[G_TILE];        // kept entries' offsets in the tile, in order, by wavefront
   __shared__ uint8_t s_code[CODES ? G_TILE : 1];
-  __shared__ uint32_t scratch[G_NT / WAVE + 2];
+  __shared__ uint32_t s_tot[2][G_NT / WAVE];   // kept entries per wavefront, this tile's and the one before
+  __shared__ uint32_t s_eq[G_NT / WAVE];
   __shared__ float s_mm[2 * (G_NT / WAVE)];
   uint32_t* st = a.state;
   const bool none = a.k == 0;
@@ -847,10 +901,13 @@ __global__ __launch_bounds__(G_NT) void k_g_emit(GlobalArgs a) {
   // payload offset comes from tcount, so the order is free.
   auto rev = [&](uint64_t i) { return a.n_tiles - 1 - i; };
   const bool pf = tiles_prefetchable(a);
+  const uint32_t wv = threadIdx.x / WAVE, lane = (uint32_t)lane_id();
+  uint16_t* const w_off = s_off + wv * G_WAVE;
   TileRaw<InT, EF> nxt;
   bool have = pf && tile_whole(a, rev(blockIdx.x));
-  if (have) tile_fetch<InT, EF>(a, rev(blockIdx.x), nxt);
-  for (uint64_t it = blockIdx.x; it < a.n_tiles; it += gridDim.x) {
+  if (have) tile_fetch<InT, EF, true>(a, rev(blockIdx.x), nxt);
+  uint32_t turn = 0;
+  for (uint64_t it = blockIdx.x; it < a.n_tiles; it += gridDim.x, turn ^= 1u) {
     const uint64_t tile = rev(it);
     // the tile's offset (from tcount), loaded together with its data
     uint32_t gt_before = 0, eq_before = 0, rec_gt = 0, rec_eq = 0;
@@ -864,62 +921,85 @@ __global__ __launch_bounds__(G_NT) void k_g_emit(GlobalArgs a) {
       gt_before = wg2.x + pre2.x;
       eq_before = wg2.y + pre2.y;
     }
-    const uint64_t t0 = tile * G_TILE + (uint64_t)threadIdx.x * G_VPT;
-    const int nv = (int)min((uint64_t)G_VPT, sat_sub(a.L, t0));
+    const bool whole = tile_whole(a, tile);
     float v[G_VPT];
     if (have) tile_values<InT, EF>(nxt, v);
-    else load_tile_values<InT, EF>(a, t0, nv, v);
+    else tile_values_any<InT, EF>(a, tile, v);
     have = pf && it + gridDim.x < a.n_tiles && tile_whole(a, rev(it + gridDim.x));
-    if (have) tile_fetch<InT, EF>(a, rev(it + gridDim.x), nxt);
-    // ---- (1) keys > T and == T as bit masks (bit i: element i); keys
-    // and T stay below 2^31, so the sign bit of a difference compares them
-    uint32_t gm = 0, em = 0;
+    if (have) tile_fetch<InT, EF, true>(a, rev(it + gridDim.x), nxt);
+    // ---- (1) keys > T and == T as bit masks (bit 4 q + i: element i of
+    // piece q); keys and T stay below 2^31, so the sign bit of a difference
+    // compares them
+    uint32_t km = 0, em = 0;
 #pragma unroll
     for (int i = 0; i < G_VPT; ++i) {
       const uint32_t kk = mag_key(v[i]);
-      gm |= ((T - kk) >> 31) << i;
+      km |= ((T - kk) >> 31) << i;
       em |= (((kk ^ T) - 1u) >> 31) << i;
     }
-    const uint32_t valid = (nv >= G_VPT) ? 0xFFFFu : ((1u << max(nv, 0)) - 1u);
-    gm &= none ? 0u : valid;
-    em &= none ? 0u : valid;
+    const uint32_t valid = none ? 0u : tile_valid(a, tile);
+    km &= valid;
+    em &= valid;
 #pragma unroll
-    for (int q = 0; q < G_VPT / 4; ++q) {
+    for (int q = 0; q < G_NP; ++q) {
       u32x4 w;
 #pragma unroll
       for (int i = 0; i < 4; ++i) w[i] = __float_as_uint(v[4 * q + i]);
-      *reinterpret_cast<u32x4*>(&s_v[threadIdx.x * G_VPT + 4 * q]) = w;
+      *reinterpret_cast<u32x4*>(&s_v[piece_at(q)]) = w;
     }
-    uint32_t tot;
-    const uint32_t ex = block_excl_scan<G_NT>((uint32_t)__builtin_popcount(gm) | ((uint32_t)__builtin_popcount(em) << 16),
-                                             scratch, tot);
-    const uint32_t gt_t = tot & 0xFFFFu, eq_t = tot >> 16;
-    if (!none && threadIdx.x == 0 && (rec_gt != gt_t || rec_eq != eq_t)) raise_error(KERR_INTERNAL);
-    // ---- placement inside the tile (ties: the lowest indices overall)
-    const uint32_t quota_t = min(sat_sub(r, eq_before), eq_t);
-    const uint32_t gt_ex = ex & 0xFFFFu, eq_ex = ex >> 16;
+    // ---- placement inside the tile.  Ties: the lowest indices overall, so
+    // all of the tile's, none, or (one tile of the segment) its first ones
+    const uint32_t quota_t = min(sat_sub(r, eq_before), rec_eq);
     const uint32_t tile_first = gt_before + min(eq_before, r);
-    const uint32_t cnt = gt_t + quota_t;
-    uint32_t tie_keep = min(sat_sub(quota_t, eq_ex), (uint32_t)G_VPT);
-    uint32_t km = gm, rest = em;             // kept: larger keys and the first tie_keep ties
-    for (; tie_keep && rest; --tie_keep) {
-      km |= rest & (0u - rest);
-      rest &= rest - 1u;
+    const uint32_t cnt = rec_gt + quota_t;
+    if (quota_t == rec_eq) {
+      km |= em;
+    } else if (quota_t > 0u) {
+      uint32_t n[G_NP], ex[G_NP];
+#pragma unroll
+      for (int q = 0; q < G_NP; ++q) n[q] = (uint32_t)__builtin_popcount((em >> (4 * q)) & 15u);
+      const uint32_t tot = wave_piece_scan(n, ex);
+      if (lane == 0) s_eq[wv] = tot;
+      __syncthreads();
+      uint32_t before = 0;
+      for (uint32_t w = 0; w < wv; ++w) before += s_eq[w];
+#pragma unroll
+      for (int q = 0; q < G_NP; ++q) {
+        uint32_t left = sat_sub(quota_t, before + ex[q]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t on = (em >> (4 * q + i)) & ((left > 0u) ? 1u : 0u);
+          km |= on << (4 * q + i);
+          left -= on;
+        }
+      }
     }
-    uint32_t lp = gt_ex + min(eq_ex, quota_t);   // position in the tile's part of the payload
-    if (lp + (uint32_t)__builtin_popcount(km) > G_TILE) {
-      raise_error(KERR_INTERNAL);
-      km = 0;
+    uint32_t n[G_NP], lp[G_NP];   // per piece: entries kept, and their first place in the wavefront's list
+#pragma unroll
+    for (int q = 0; q < G_NP; ++q) n[q] = (uint32_t)__builtin_popcount((km >> (4 * q)) & 15u);
+    const uint32_t n_w = wave_piece_scan(n, lp);
+    if (lane == 0) s_tot[turn][wv] = n_w;
+#pragma unroll
+    for (int q = 0; q < G_NP; ++q) {
+      uint32_t p = lp[q];
+      for (uint32_t m = (km >> (4 * q)) & 15u; m; m &= m - 1u) w_off[p++] = (uint16_t)(piece_at(q) + (uint32_t)__builtin_ctz(m));
     }
-    for (uint32_t m = km; m; m &= m - 1u) s_off[lp++] = (uint16_t)(threadIdx.x * G_VPT + (uint32_t)__builtin_ctz(m));
     if (a.blk && threadIdx.x == 0) a.blk[tile] = tile_first;
-    __syncthreads();
-    // ---- (2) the tile's kept entries, compacted: payload, and the
+    __syncthreads();   // (and the codes of the tile before have left)
+    uint32_t first = 0, total = 0;   // the wavefront's entries start here in the tile's list
+#pragma unroll
+    for (uint32_t w = 0; w < G_NT / WAVE; ++w) {
+      const uint32_t x = s_tot[turn][w];
+      first += (w < wv) ? x : 0u;
+      total += x;
+    }
+    // ---- (2) the wavefront's kept entries, compacted: payload, and the
     // residual at their places in LDS
     const uint32_t n_ok = (uint32_t)min((uint64_t)cnt, sat_sub(a.k, (uint64_t)tile_first));
-    if (n_ok < cnt && threadIdx.x == 0) raise_error(KERR_INTERNAL);
-    for (uint32_t j = threadIdx.x; j < n_ok; j += G_NT) {
-      const uint32_t off = s_off[j];
+    if ((n_ok < cnt || total != cnt) && threadIdx.x == 0) raise_error(KERR_INTERNAL);
+    const uint32_t w_ok = min(n_w, sat_sub(n_ok, first));
+    for (uint32_t jl = lane; jl < w_ok; jl += WAVE) {
+      const uint32_t off = w_off[jl], j = first + jl;
       const float x = __uint_as_float(s_v[off]);
       const uint64_t g = (uint64_t)tile_first + j;
       a.idx[g] = (uint32_t)(tile * G_TILE + off);
@@ -945,24 +1025,28 @@ __global__ __launch_bounds__(G_NT) void k_g_emit(GlobalArgs a) {
         if (enc) s_v[off] = __float_as_uint(x - through<InT>(rec));
       }
     }
-    __syncthreads();
-    if constexpr (CODES) {
-      if (pre) write_codes<Q>(a.codes, a.wpg, tile_first, n_ok, s_code, true);
-    }
-    // ---- (3) the dense residual; write-back stores: the four 16-byte
-    // stores of a thread fill each 128-byte line only together, which the
-    // L2 merges before writing it
+    // ---- (3) the dense residual, each wavefront its own elements (its LDS
+    // accesses complete in program order)
+    __builtin_amdgcn_wave_barrier();
     if constexpr (EF) {
-      float res[G_VPT];
+      float* const ec = a.e + tile * G_TILE;
 #pragma unroll
-      for (int q = 0; q < G_VPT / 4; ++q) {
-        const u32x4 w = *reinterpret_cast<const u32x4*>(&s_v[threadIdx.x * G_VPT + 4 * q]);
+      for (int q = 0; q < G_NP; ++q) {
+        const uint32_t at = piece_at(q);
+        const u32x4 w = *reinterpret_cast<const u32x4*>(&s_v[at]);
+        if (whole && pf) {
+          vstore<true>(reinterpret_cast<u32x4*>(ec + at), w);
+        } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) res[4 * q + i] = __uint_as_float(w[i]);
+          for (int i = 0; i < 4; ++i)
+            if (tile * G_TILE + at + (uint32_t)i < a.L) ec[at + i] = __uint_as_float(w[i]);
+        }
       }
-      if (nv > 0) store_run_partial<float, G_VPT, false>(a.e + t0, nv, res);
     }
-    __syncthreads();
+    if constexpr (CODES) {
+      __syncthreads();
+      if (pre) write_codes<Q>(a.codes, a.wpg, tile_first, min(n_ok, total), s_code, true);
+    }
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     if (a.blk) a.blk[a.n_tiles] = (uint32_t)a.k;

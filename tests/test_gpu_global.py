@@ -88,6 +88,20 @@ def test_topk_quant_k_edges(tc, orc, k):
     tq_steps(tc, orc, xs, 1, L, 3)
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_topk_quant_ties_cut_inside_a_tile(tc, orc, dt):
+    # three magnitudes; the last kept tie sits at either side of the places
+    # where a tile's wavefronts (1024 elements) and pieces (256) meet, and in
+    # a ragged last tile
+    L = 2 * 4096 + 1500
+    g = torch.Generator().manual_seed(13)
+    mag = torch.randint(1, 4, (L,), generator=g).float()
+    x = (mag * (torch.randint(0, 2, (L,), generator=g) * 2 - 1)).to(TORCH[dt])
+    above, at = (mag > 2).sum().item(), (mag == 2).cumsum(0)
+    for end in (1, 255, 256, 1023, 1024, 1025, 4095, 4096, 2 * 4096 + 1024, L - 1):
+        tq_steps(tc, orc, [x], 1, above + max(1, at[end].item()), 4)
+
+
 def test_topk_quant_constant_group(tc, orc):
     # every kept value equal (hi == lo): scale 0, all codes 0
     L = 4096 + 17
