@@ -164,13 +164,16 @@ __global__ __launch_bounds__(NT, pack_waves(sizeof(typename Elem<InT>::raw) == 4
   const uint64_t base = (uint64_t)part * CH;   // the chunk's first element in its group
   const bool vec = (((uintptr_t)a.x | (uintptr_t)a.e) & 15u) == 0 && (a.G % QPE) == 0;
   // piece j of this thread, in the chunk; the elements the chunk holds
-  auto piece_at = [&](int j) -> uint32_t { return ((uint32_t)(j * NT) + threadIdx.x) * QPE; };
+  uint32_t tid = threadIdx.x;
+  auto piece_at = [&](int j) -> uint32_t { return ((uint32_t)(j * NT) + tid) * QPE; };
   const uint32_t n_here = (uint32_t)min(CH, sat_sub(a.G, base));
   auto piece_n = [&](int j) -> int { return (int)min((uint32_t)QPE, sat_sub(n_here, piece_at(j))); };
   // some thread's piece j holds elements of the group (the same for all threads)
   auto live = [&](int j) -> bool { return (uint32_t)(j * NT * QPE) < n_here; };
 
   for (uint64_t grp = group; grp < a.n_grp; grp += n_groups, ++it) {
+    // (addresses are computed where they are used, not ahead of the loop)
+    asm volatile("" : "+v"(tid));
     const R* const xc = (const R*)a.x + grp * a.G + base;
     float* const ec = EF ? a.e + grp * a.G + base : nullptr;
     float v[QVPT] = {};
@@ -199,24 +202,50 @@ __global__ __launch_bounds__(NT, pack_waves(sizeof(typename Elem<InT>::raw) == 4
           }
         }
       }
-    } else {
+    } else if (a.G >= QPE) {
+      // aligned to elements only (with a load per element, each under a test of
+      // its own, 3 x 80,129 binary32 with EF took 17.6 us a micro-batch with its
+      // receiver, now 15.4): a piece across the group's end reads its
+      // last four elements and moves those it holds to the front (one past
+      // the end is unused)
+      const R* const xg = xc - base;
+      const float* const eg = EF ? ec - base : nullptr;
 #pragma unroll
-      for (int j = 0; j < QNP; ++j) {
-        const int n = piece_n(j);
-        R xr[QPE];
-        float er[QPE];
-        if (n > 0) {
-          load_run_partial<R, QPE, true>(xc + piece_at(j), n, R{}, xr);
-          if constexpr (EF) load_run_partial<float, QPE, true>(ec + piece_at(j), n, 0.0f, er);
+      for (int h = 0; h < QNP; h += QNP / 2) {
+        if (!live(h)) continue;
+        R xr[QNP / 2][QPE];
+        float er[QNP / 2][QPE];
+#pragma unroll
+        for (int j = 0; j < QNP / 2; ++j) {
+          const uint64_t at = min(base + piece_at(h + j), a.G - QPE);
+          load_piece_any<R>(xg + at, xr[j]);
+          if constexpr (EF) load_piece_any<float>(eg + at, er[j]);
         }
 #pragma unroll
-        for (int i = 0; i < QPE; ++i) {
-          float t = 0.0f;
-          if (i < n) {
-            t = Elem<InT>::up(xr[i]);
-            if constexpr (EF) t = t + er[i];
+        for (int j = 0; j < QNP / 2; ++j) {
+          const uint32_t sh = (uint32_t)sat_sub(base + piece_at(h + j), a.G - QPE);
+#pragma unroll
+          for (int i = 0; i < QPE; ++i) {
+            float t = Elem<InT>::up(xr[j][i]);
+            if constexpr (EF) t = t + er[j][i];
+            v[(h + j) * QPE + i] = t;
           }
-          v[j * QPE + i] = t;
+          float* const w = &v[(h + j) * QPE];
+          const bool one = (sh & 1u) != 0u, two = (sh & 2u) != 0u;
+          w[0] = one ? w[1] : w[0];
+          w[1] = one ? w[2] : w[1];
+          w[2] = one ? w[3] : w[2];
+          w[0] = two ? w[2] : w[0];
+          w[1] = two ? w[3] : w[1];
+        }
+      }
+    } else if (tid == 0) {
+      // (fewer than four elements)
+#pragma unroll
+      for (int i = 0; i < QPE; ++i) {
+        if ((uint64_t)i < a.G) {
+          v[i] = Elem<InT>::up(xc[i]);
+          if constexpr (EF) v[i] = v[i] + ec[i];
         }
       }
     }
@@ -501,7 +530,13 @@ SegPlan plan_quant(int dt, uint32_t bits, bool ef, uint64_t n_grp, uint64_t G) {
   p.nt = (G <= (uint64_t)ROW_NT * QVPT) ? ROW_NT : BIG_NT;
   const uint64_t CH = (uint64_t)p.nt * QVPT;
   p.P = (uint32_t)((G + CH - 1) / CH);
-  const uint64_t cap = (uint64_t)std::max(1, resident_per_cu(pick_pack(dt, bits, ef, p.nt), p.nt)) * cus;
+  // the longest group that is taken does not follow the registers an instance
+  // happens to need: as many workgroups as pack_waves sets aside for, four
+  // where the values only pass through
+  int per_cu = std::max(1, resident_per_cu(pick_pack(dt, bits, ef, p.nt), p.nt));
+  if (p.nt == BIG_NT)
+    per_cu = std::min(per_cu, (bits == 32 && !ef) ? 4 : pack_waves(dt == DT_F32, (int)bits, ef, BIG_NT) * 4 / (BIG_NT / WAVE));
+  const uint64_t cap = (uint64_t)per_cu * cus;
   p.capacity = cap;
   const uint64_t groups = std::min<uint64_t>(n_grp, std::max<uint64_t>(1, cap / p.P));
   p.n_groups = (uint32_t)groups;

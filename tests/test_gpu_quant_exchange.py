@@ -31,3 +31,25 @@ def test_exchange_parity(tc, orc, n_grp, G, dt, bits):
         assert_bits_equal(raw(meta), np.asarray(om).reshape(n_grp, 2), f"meta {what}")
         assert_bits_equal(raw(e).reshape(n_grp, G), np.asarray(eo).reshape(n_grp, G), f"e {what}")
     assert tc.device_errors() == 0
+
+
+@pytest.mark.parametrize("G", [1, 2, 3, 5, 6, 7, 2045, 2047, 2050, 16383, 16387, 32771])
+@pytest.mark.parametrize("dt,bits,off", [("f32", 4, 0), ("bf16", 2, 1), ("f16", 32, 3)])
+def test_unaligned_groups(tc, orc, G, dt, bits, off):
+    """groups that end inside a piece of four elements, at addresses aligned to
+    their elements only"""
+    n = 3
+    g = torch.Generator().manual_seed(G)
+    x = torch.randn((n, G), generator=g).to(TORCH[dt])
+    e0 = torch.randn((n, G), generator=g) * 0.1
+    xd = torch.empty(n * G + 8, dtype=TORCH[dt], device="cuda")[off:off + n * G].view(n, G)
+    ed = torch.empty(n * G + 8, device="cuda")[off:off + n * G]
+    xd.copy_(x)
+    ed.copy_(e0.reshape(-1))
+    codes, meta = tc.ef_step_quant(xd, ed, bits, n)
+    torch.cuda.synchronize()
+    oc, om, eo = orc.ef_quant(raw(x), dt, e0.numpy(), n, G, bits)
+    assert np.array_equal(codes.cpu().numpy().ravel(), np.asarray(oc).view(np.uint8).ravel()), "codes"
+    assert_bits_equal(raw(meta), np.asarray(om).reshape(n, 2), "meta")
+    assert_bits_equal(raw(ed).reshape(n, G), np.asarray(eo).reshape(n, G), "e")
+    assert tc.device_errors() == 0
