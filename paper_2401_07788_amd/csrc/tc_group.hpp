@@ -17,7 +17,7 @@
 //      key, and adds its counts from an octave below that bin upwards into the
 //      group's histogram, its guess into the group's smallest and largest
 //      guess, and 32 finer counts (bits 18..14) of the guessed bin and its two
-//      neighbours.  After the barrier, one read of the merged counts gives the
+//      neighbours (bins 0 to 2 when it guesses bin 0).  After the barrier, one read of the merged counts gives the
 //      bin b1 (exact when no guess lies more than an octave above it: then no
 //      count at or above b1 is missing) and, when every guess was within one
 //      bin of b1, the 17-bit prefix of T.
@@ -314,8 +314,10 @@ __device__ __forceinline__ SelA grp_exchange_a(float (&v)[R][E], uint32_t zc, ui
   const uint32_t need_loc = (uint32_t)min<uint64_t>(max<uint64_t>(((uint64_t)k * n_loc + L - 1) / L, 1), n_loc);
   find_bin<NT, HIST_BINS>(sh.hist, need_loc, sm.scratch, sm.found);
   const uint32_t bh = sm.found[0];
+  // the window: three bins in every workgroup, whatever it guesses (none lies
+  // above the last bin), which is what the test of b1 below takes for granted
   const uint32_t lo = bh > 0u ? bh - 1u : 0u;
-  const uint32_t hi = min(bh + 1u, (uint32_t)HIST_BINS - 1u);
+  const uint32_t hi = min(lo + 2u, (uint32_t)HIST_BINS - 1u);
   // bits 18..14 of the keys in bins lo..hi (the exact zeros, whose bits
   // 18..14 are 0, once per wave)
   refresh(v);
@@ -365,7 +367,8 @@ __device__ __forceinline__ SelA grp_exchange_a(float (&v)[R][E], uint32_t zc, ui
     const uint32_t c = (lane < FINE_N) ? sm.fmrg[(b1 - lo) * FINE_N + (FINE_N - 1u - lane)] : 0u;
     const uint32_t incl = wave_incl_scan(c);
     const uint64_t hit = __ballot(lane < FINE_N && incl >= need);
-    const int l = hit ? __builtin_ctzll(hit) : 0;   // (a hit is certain: the counts are complete)
+    if (hit == 0 && t == 0) raise_error(KERR_INTERNAL);   // (the counts are complete: a hit is certain)
+    const int l = hit ? __builtin_ctzll(hit) : 0;
     A.prefix = (b1 << FINE_BITS) | (FINE_N - 1u - (uint32_t)l);
     A.pbits = 12 + FINE_BITS;
     A.need = need - (uint32_t)__builtin_amdgcn_readlane((int)(incl - c), l);

@@ -5,7 +5,7 @@ resident at once, every layout (runs per thread), and data that takes each way
 through the exchanges -- chunks whose magnitudes differ by octaves (the
 window guesses miss), a gap around the threshold, ties in one key per
 workgroup (multiplicities), many distinct keys on the prefix (records
-overflow), all zeros."""
+overflow), all zeros, thresholds among the subnormals."""
 import pytest
 import torch
 
@@ -55,6 +55,47 @@ def test_group_parity(tc, orc, n_seg, L, dt, kind):
         assert_bits_equal(raw(pl.val), ov, f"val {what}")
         assert_bits_equal(raw(ed).reshape(n_seg, L), oe, f"e {what}")
         check_block_table(pl.blk, oi, L, what)
+    assert tc.device_errors() == 0
+
+
+def tiny(shape, dt, b, seed):
+    """zeros and, denser in the first half of a segment than in the second,
+    subnormal or barely normal magnitudes whose key has b in bits 30..19"""
+    g = torch.Generator().manual_seed(seed)
+    p = torch.where(torch.arange(shape[-1]) < shape[-1] // 2, 0.13, 0.08)
+    low = torch.randint(0 if b else 1, 1 << 19, shape, generator=g)
+    key = torch.where(torch.rand(shape, generator=g) < p, (b << 19) + low, 0)
+    key += torch.randint(0, 2, shape, generator=g) << 31
+    if dt == "bf16":
+        return (key >> 16).to(torch.int32).to(torch.int16).view(torch.bfloat16)
+    return torch.where(key >= 1 << 31, key - (1 << 32), key).to(torch.int32).view(torch.float32)
+
+
+@pytest.mark.parametrize("b", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("L,dt", [(40000, "f32"), (70001, "f32"), (40000, "bf16"), (70001, "bf16")])
+def test_group_threshold_near_zero(tc, orc, L, dt, b):
+    """k-th magnitudes in the lowest bins of the first histogram: with k a tenth
+    of the segment the workgroups of its first half guess bin b and those of
+    its second half bin 0, whose window has no neighbour below"""
+    n, k = 2, L // 10
+    x = tiny((n, L), dt, b, 11)
+    ids = torch.arange(n, dtype=torch.int64)
+    ed, eo = torch.zeros(n * L, device="cuda"), torch.zeros(n, L).numpy()
+    md = torch.zeros((n, L), dtype=TORCH[dt], device="cuda")
+    mo = raw(md).copy()
+    plain = tc.topk_compress(x.cuda(), k, n)
+    ef = tc.ef_step_topk(x.cuda(), ed, k, n)
+    aq = tc.aqsgd_step(x.cuda(), md, ids.cuda(), k)
+    torch.cuda.synchronize()
+    pi, pv = orc.topk_compress(raw(x), dt, n, L, k)
+    oi, ov, oe = orc.ef_topk(raw(x), dt, eo, n, L, k)
+    ai, av = orc.aqsgd_send(raw(x), mo, dt, ids.numpy(), k)
+    for what, pl, wi, wv in (("plain", plain, pi, pv), ("EF", ef, oi, ov), ("AQ-SGD", aq, ai, av)):
+        assert_bits_equal(raw(pl.idx), wi, f"idx {what}")
+        assert_bits_equal(raw(pl.val), wv, f"val {what}")
+        check_block_table(pl.blk, wi, L, what)
+    assert_bits_equal(raw(ed).reshape(n, L), oe, "e")
+    assert_bits_equal(raw(md), mo, "m")
     assert tc.device_errors() == 0
 
 
