@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace tc {
 
 constexpr int WAVE = 64;
@@ -190,18 +192,31 @@ __device__ __forceinline__ void load_piece(const Raw* p, Raw (&out)[4]) {
 
 // the same for a piece aligned to its elements only (the hardware takes
 // unaligned vector accesses; a piece across a line costs a second request)
-template <typename Raw>
+typedef u32x4 u32x4_any __attribute__((aligned(4)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+template <typename Raw, bool STREAM = false>
 __device__ __forceinline__ void load_piece_any(const Raw* p, Raw (&out)[4]) {
-  struct __attribute__((packed, aligned(sizeof(Raw)))) Piece { Raw v[4]; };
-  const Piece w = *reinterpret_cast<const Piece*>(p);
-  __builtin_memcpy(out, &w, sizeof(w));
+  const auto* const q = reinterpret_cast<std::conditional_t<sizeof(Raw) == 4, const u32x4_any, const u32x2_any>*>(p);
+  if constexpr (STREAM) {
+    const auto w = __builtin_nontemporal_load(q);
+    __builtin_memcpy(out, &w, sizeof(w));
+  } else {
+    const auto w = *q;
+    __builtin_memcpy(out, &w, sizeof(w));
+  }
 }
-template <typename Raw>
+template <typename Raw, bool STREAM = false>
 __device__ __forceinline__ void store_piece_any(Raw* p, const Raw (&in)[4]) {
-  struct __attribute__((packed, aligned(sizeof(Raw)))) Piece { Raw v[4]; };
-  Piece w;
+  using V = std::conditional_t<sizeof(Raw) == 4, u32x4, u32x2>;
+  V w;
   __builtin_memcpy(&w, in, sizeof(w));
-  *reinterpret_cast<Piece*>(p) = w;
+  if constexpr (sizeof(Raw) == 4) {
+    if constexpr (STREAM) __builtin_nontemporal_store(w, reinterpret_cast<u32x4_any*>(p));
+    else *reinterpret_cast<u32x4_any*>(p) = w;
+  } else {
+    if constexpr (STREAM) __builtin_nontemporal_store(w, reinterpret_cast<u32x2_any*>(p));
+    else *reinterpret_cast<u32x2_any*>(p) = w;
+  }
 }
 
 // Load a run that may be cut short at `n` valid elements (n <= N); elements

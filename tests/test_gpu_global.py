@@ -102,6 +102,32 @@ def test_topk_quant_ties_cut_inside_a_tile(tc, orc, dt):
         tq_steps(tc, orc, [x], 1, above + max(1, at[end].item()), 4)
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("off_x,off_e", [(1, 0), (0, 1), (3, 2)])
+@pytest.mark.parametrize("n_seg,L", [(1, 4096), (1, 3 * 4096 + 1), (3, 4099), (2, 2 * 4096 - 1)])
+def test_topk_quant_unaligned(tc, orc, dt, off_x, off_e, n_seg, L):
+    """arrays aligned to their elements only, whole and cut tiles, over two
+    steps: the elements beside the residual stay as they are"""
+    k, n = tc.topk_count(L, 1, 10), n_seg * L
+    xd = torch.empty(n + 8, dtype=TORCH[dt], device="cuda")[off_x:off_x + n]
+    eb = torch.full((n + 8,), 3.0, device="cuda")
+    ed = eb[off_e:off_e + n]
+    ed.zero_()
+    eo = np.zeros((n_seg, L), np.float32)
+    for t in range(2):
+        x = W.randn((n_seg, L), 17, t).to(TORCH[dt])
+        xd.copy_(x.reshape(-1))
+        p = tc.ef_step_topk_quant(xd, ed, k, 4, n_seg)
+        torch.cuda.synchronize()
+        oi, oc, om, eo = orc.ef_topk_quant(raw(x), dt, eo, n_seg, L, k, 4)
+        assert_bits_equal(raw(p.idx), oi, f"idx step {t}")
+        assert_bits_equal(raw(p.meta), om, f"meta step {t}")
+        assert_bits_equal(raw(p.codes), oc, f"codes step {t}")
+        assert_bits_equal(raw(ed).reshape(n_seg, L), eo, f"e step {t}")
+    assert (eb[:off_e] == 3.0).all() and (eb[off_e + n:] == 3.0).all()
+    assert tc.device_errors() == 0
+
+
 def test_topk_quant_constant_group(tc, orc):
     # every kept value equal (hi == lo): scale 0, all codes 0
     L = 4096 + 17
