@@ -101,8 +101,9 @@ __global__ __launch_bounds__(WAVE) void k_topk_row(TopkArgs a) {
   constexpr int V = 4 * NP;
   __shared__ RowStage<R, NP> st;
   const uint32_t L = (uint32_t)a.L, k = (uint32_t)a.k;
-  const float lL = __builtin_amdgcn_logf((float)L), lk = __builtin_amdgcn_logf((float)max(k, 1u));
-  const RowLogs lg{lk, lL, 0.95f * 0.6931472f * __builtin_amdgcn_logf((float)L * __builtin_amdgcn_rcpf((float)max(k, 1u)) + 0.15f)};
+  // the selection's guess: magnitudes exponentially distributed around their
+  // mean, 0.95 ln(L / k + 0.15) times it
+  const float lg = 0.95f * 0.6931472f * __builtin_amdgcn_logf((float)L * __builtin_amdgcn_rcpf((float)max(k, 1u)) + 0.15f);
   const float rl = __builtin_amdgcn_rcpf((float)L);
   const bool vec = (((uintptr_t)a.x | (uintptr_t)a.e | (uintptr_t)a.m) & 15u) == 0 && (L % 4u) == 0;
   for (uint64_t seg = blockIdx.x; seg < a.n_seg; seg += gridDim.x) {
@@ -197,7 +198,9 @@ __global__ __launch_bounds__(WAVE) void k_topk_row(TopkArgs a) {
         if constexpr (SEL == SEL_PLAIN) tz = std::is_same<InT, bf16_t>::value ? 16u : 13u;
         if constexpr (SEL == SEL_AQSGD) tz = (uint32_t)__builtin_ctz(wave_or(bits) | (1u << RW_SHIFT));
       }
-      const uint32_t T = wave_select_key<V>(key, L, k, tz, wave_fsum(sum) * rl, lg, st.hist);
+      // (positive or 0, or a NaN: below 2^31 either way once the sign is off)
+      const uint32_t t0 = __float_as_uint(wave_fsum(sum) * rl * lg) & 0x7FFFFFFFu;
+      const uint32_t T = wave_select_key<V>(key, k, tz, (uint32_t)__builtin_amdgcn_readfirstlane((int)t0), st.hist);
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
 #pragma unroll
@@ -207,7 +210,7 @@ __global__ __launch_bounds__(WAVE) void k_topk_row(TopkArgs a) {
       const uint32_t total = row_scan<NP>(n, ex);
       if (total != k) {
         // more keys equal to T than are kept: the lowest-indexed ones are
-        uint32_t em[NP];
+        uint32_t em[NP], eq[NP];
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
           em[p] = 0u;
@@ -215,20 +218,20 @@ __global__ __launch_bounds__(WAVE) void k_topk_row(TopkArgs a) {
           for (int i = 0; i < 4; ++i) em[p] |= eq31(key[4 * p + i], T) << i;
           n[p] = (uint32_t)__builtin_popcount(em[p]);
         }
-        const uint32_t ties = row_scan<NP>(n, ex);
-        const uint32_t r = k - min(k, total - ties);
+        const uint32_t ties = row_scan<NP>(n, eq);
+        const uint32_t r = k - min(k, total - ties);   // ties kept
+        if (total < k && lane == 0) raise_error(KERR_INTERNAL);
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-          uint32_t left = sat_sub(r, ex[p]);
+          uint32_t left = sat_sub(r, eq[p]);
+          ex[p] -= eq[p] - min(eq[p], r);
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const uint32_t tie = (em[p] >> i) & 1u, on = tie & gt31(left, 0u);
             km[p] &= ~((tie ^ on) << i);
             left -= on;
           }
-          n[p] = (uint32_t)__builtin_popcount(km[p]);
         }
-        if (row_scan<NP>(n, ex) != k && lane == 0) raise_error(KERR_INTERNAL);
       }
     }
 

@@ -97,171 +97,174 @@ __device__ __forceinline__ void zero_lds(uint32_t* h, int n) {
   for (int b = (int)threadIdx.x; b < n; b += NT) h[b] = 0u;
 }
 
-// The threshold by counting: C(t) = #(key >= t) over the segment for a few
-// trial keys t, which narrow a bracket lo < hi with C(lo) > k > C(hi) (or lo
-// = 0, hi = 2^31).  Every lane holds the same values, on the scalar unit but
-// for the guess itself.  Trials are guessed from the counts: the first as if
-// magnitudes were exponentially distributed around their mean mu, then by
-// interpolation of log C between the ends, in value where the bracket spans
-// octaves (a heavy tail or a mass at zero bends log C there), in key
-// otherwise.  From the eighth trial on each halves the bracket in key, which
-// bounds the search at 39 trials for any input.  Keys are multiples of 2^tz,
-// and so are lo and hi: 16-bit inputs need no search below their last bit.
-// Only which t is tried depends on floating point; the counts decide.
-struct CountSearch {
-  uint32_t lo = 0u, hi = 0x80000000u;   // trial keys: C(lo) = cl, C(hi) = ch
-  uint32_t cl, ch = 0u, n = 0u;
-  uint32_t k, tz;
-  float mu, lk, la, lb = -1.0f;         // log2 of k, cl, ch (of 1/2 for ch = 0)
-  __device__ __forceinline__ CountSearch(uint32_t L, uint32_t k_, uint32_t tz_, float mu_, float lk_, float lL)
-      : cl(L), k(k_), tz(tz_), mu(mu_), lk(lk_), la(lL) {}
-  __device__ __forceinline__ bool closed() const { return hi - lo <= (1u << tz); }   // T = lo, k - ch ties kept
-  // a key strictly inside the bracket, a multiple of 2^tz, near t
-  __device__ __forceinline__ uint32_t inside(uint32_t t) const {
-    const uint32_t g = 1u << tz;
-    t = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
-    t = min(max(t, lo), hi - 1u);
-    t = lo + max(g, ((t - lo) >> tz) << tz);
-    return min(t, hi - g);
-  }
-  // lg = 0.95 ln(L / k + 0.15)
-  __device__ __forceinline__ uint32_t first(float lg) const { return inside(__float_as_uint(mu * lg)); }
-  __device__ __forceinline__ void update(uint32_t t, uint32_t c) {
-    const float l = c ? __builtin_amdgcn_logf((float)c) : -1.0f;
-    // (selects, one per member: branches would leave the object in memory)
-    const bool low = c > k;
-    lo = low ? t : lo;
-    cl = low ? c : cl;
-    la = low ? l : la;
-    hi = low ? hi : t;
-    ch = low ? ch : c;
-    lb = low ? lb : l;
-    ++n;
-  }
-  __device__ __forceinline__ uint32_t next() const {
-    constexpr float LN2 = 0.6931472f;
-    if (n >= 8u) return inside(lo + ((hi - lo) >> 1));
-    if (hi == 0x80000000u)                // no upper end yet: out by the mean, doubling
-      return inside(__float_as_uint(__uint_as_float(lo) + mu * LN2 * (la - lk) * (float)(1u << (n - 1u))));
-    if (lo == 0u) {                       // no lower end yet: down once, then "not zero"
-      if (n >= 2u) return inside(1u);
-      const float h = __uint_as_float(hi);
-      return inside(__float_as_uint(fmaxf(h - 1.1f * mu * LN2 * (lk - lb), 0.25f * h)));
-    }
-    const float f = (la - lk) * __builtin_amdgcn_rcpf(la - lb);
-    if (hi - lo > (1u << 24) && (n & 1u) == 0u) {
-      const float l = __uint_as_float(lo);
-      return inside(__float_as_uint(l + (__uint_as_float(hi) - l) * f));
-    }
-    return inside(lo + (uint32_t)((float)(hi - lo) * f));
-  }
-};
-
 // Exact threshold for a segment held by one wavefront, V keys per lane (keys
 // past the segment's L are 0 and come after it): the k-th largest key T, or
 // any T' with exactly k keys at or above it.  Four rows share a SIMD, so what
-// counts is instructions issued: a trial key costs two per key for one bit of
-// T, a histogram five for nine bits.  So the first guess places a window of
-// two octaves on either side of it, 512 bins of 1/128 octave (one to four keys
-// of a row each around T), counted with LDS atomics (keys below the window in
-// a word per lane, so that they do not meet in one); T's bin then gives up
-// its keys from the nearer end, a wavefront reduction each.  A window that
-// missed T, or a bin with many keys, leaves the rest to trial keys.
-// 1 <= k <= L; tz as above, at most RW_SHIFT.
+// counts is instructions issued.  A first guess t0 places a window of two
+// octaves on either side of it, 512 bins of 1/128 octave (one to four keys of a
+// row each around T), counted with LDS atomics (keys below the window in a word
+// per lane, so that they do not meet in one).  T's bin then gives up its keys
+// from the nearer end, a wavefront reduction each: at once where it holds a
+// few, and once in any case, as values that repeat fill a bin with one key.
+// What is left, or what lies beyond the window when it missed T, is split into
+// 512 bins again (five or six instructions per key for nine bits of T, at most
+// six such passes for any input).  4096 x 768 bfloat16 with EF, 10 %: 17
+// distinct values 19.7 us, values with a gap at T 15.6 when trial keys stood in
+// place of these passes (two instructions per key for about a bit each), 12.2
+// and 10.0 now; normal data 9.8 both ways.  Two cases go without the window:
+// k up to 2 takes the largest keys (every key in one bin, k = 1: 16.7 us with
+// it, 6 to 7 without), and where the lanes' first keys share a bin the keys
+// are taken to be nearly alike (all of a bin's lanes add to one word in turn).
+// Keys are multiples of 2^tz (tz <= RW_SHIFT), and so are lo and hi: 16-bit
+// inputs need no search below their last bit.  1 <= k <= L.
 constexpr uint32_t RW_BINS = 512, RW_SHIFT = 16;            // 2^25: four octaves
+constexpr uint32_t RW_WIDE = 27;                            // 2^27: 16 octaves
 constexpr uint32_t RW_WORDS = RW_BINS + WAVE;               // LDS words (16-byte aligned)
-struct RowLogs {
-  float lk, lL, lg;   // log2 k, log2 L, the first guess's factor
-};
-template <int V>
-__device__ __forceinline__ uint32_t wave_select_key(const uint32_t (&key)[V], uint32_t L, uint32_t k, uint32_t tz,
-                                                    float mu, const RowLogs& lg, uint32_t* hist) {
-  CountSearch s(L, k, tz, mu, lg.lk, lg.lL);
-  const uint32_t t0 = s.first(lg.lg);
+
+// T's bin, the keys in larger bins and its own keys, of 512 bins in which
+// `need` is the rank from the top; false when they do not reach it (above:
+// what they hold)
+__device__ __forceinline__ bool row_find_bin(const uint32_t* bins, uint32_t need, uint32_t& bin, uint32_t& above,
+                                             uint32_t& cnt) {
   const uint32_t lane = (uint32_t)lane_id();
-  {
-    const uint32_t base = (t0 - min(t0, 2u << 23)) & ~((1u << RW_SHIFT) - 1u);
-    uint32_t* const bins = hist + WAVE;
+  const u32x4 h0 = reinterpret_cast<const u32x4*>(bins)[2 * lane], h1 = reinterpret_cast<const u32x4*>(bins)[2 * lane + 1];
+  const uint32_t h[8] = {h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w};
+  const uint32_t sum = ((h[0] + h[1]) + (h[2] + h[3])) + ((h[4] + h[5]) + (h[6] + h[7]));
+  const uint32_t incl = wave_incl_scan(sum);
+  const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
+  uint32_t acc = all - incl;          // keys in bins of higher lanes
+  const uint64_t here = __ballot(acc < need && need <= acc + sum);
+  above = all;
+  if (!here) return false;
+  const int src = __builtin_ctzll(here);
+  uint32_t ab = acc, bi = 0u, cn = 0u;
+#pragma unroll
+  for (int c = 7; c >= 0; --c) {
+    const bool on = acc < need;       // the last such bin, from the top, is T's
+    ab = on ? acc : ab;
+    bi = on ? (uint32_t)c : bi;
+    cn = on ? h[c] : cn;
+    acc += h[c];
+  }
+  bin = 8u * (uint32_t)src + (uint32_t)__builtin_amdgcn_readlane((int)bi, src);
+  above = (uint32_t)__builtin_amdgcn_readlane((int)ab, src);
+  cnt = (uint32_t)__builtin_amdgcn_readlane((int)cn, src);
+  return true;
+}
+
+template <int V>
+__device__ __forceinline__ uint32_t wave_select_key(const uint32_t (&key)[V], uint32_t k, uint32_t tz, uint32_t t0,
+                                                    uint32_t* hist) {
+  const uint32_t lane = (uint32_t)lane_id(), unit = 1u << tz;
+  uint32_t* const bins = hist + WAVE;
+  const int below = -1 - (int)lane;   // this lane's word for keys that are not counted
+  auto clear = [&] {
     reinterpret_cast<u32x4*>(bins)[lane] = u32x4{0u, 0u, 0u, 0u};
     reinterpret_cast<u32x4*>(bins)[lane + WAVE] = u32x4{0u, 0u, 0u, 0u};
     __builtin_amdgcn_wave_barrier();
-    const int below = -1 - (int)lane;
+  };
+  // the bracket of T: C(t) = #(key >= t) is ch < k at hi and, once counted,
+  // cl >= k at lo; lo is 0 or above it
+  uint32_t lo = 0u, hi = 0x80000000u, cl = 0u, ch = 0u;
+  uint32_t bin, above, cnt;
+  bool split = true;                  // the bracket is to be split before its keys are looked at
+  const uint32_t base = (t0 - min(t0, 2u << 23)) & ~((1u << RW_SHIFT) - 1u);
+  const int b0 = (int)(key[0] - base) >> RW_SHIFT;
+  if (k <= 2u) {
+    split = false;                    // the largest keys
+  } else if (__ballot(b0 == __builtin_amdgcn_readfirstlane(b0)) == ~0ull) {
+    // (nearly) one value throughout: its lanes would all meet in one word;
+    // from the smallest key that is not 0 to the largest instead
+    uint32_t small = ~0u, large = 0u;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      small = min(small, key[i] - 1u);
+      large = max(large, key[i]);
+    }
+    lo = wave_uminmax<false>(small) + 1u;
+    hi = wave_uminmax<true>(large) + unit;
+  } else {
+    clear();
 #pragma unroll
     for (int i = 0; i < V; ++i) {
       const int b = (int)(key[i] - base) >> RW_SHIFT;
       atomicAdd(&bins[min(max(b, below), (int)RW_BINS - 1)], 1u);
     }
     __builtin_amdgcn_wave_barrier();
-    const u32x4 h0 = reinterpret_cast<const u32x4*>(bins)[2 * lane], h1 = reinterpret_cast<const u32x4*>(bins)[2 * lane + 1];
-    const uint32_t h[8] = {h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w};
-    const uint32_t sum = ((h[0] + h[1]) + (h[2] + h[3])) + ((h[4] + h[5]) + (h[6] + h[7]));
-    const uint32_t incl = wave_incl_scan(sum);
-    uint32_t acc = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1) - incl;   // keys in bins of higher lanes
-    const uint64_t here = __ballot(acc < k && k <= acc + sum);
-    if (here) {
-      const int src = __builtin_ctzll(here);
-      uint32_t above = acc, bin = 0u, cnt = 0u;
-#pragma unroll
-      for (int c = 7; c >= 0; --c) {
-        const bool on = acc < k;          // the last such bin, from the top, is T's
-        above = on ? acc : above;
-        bin = on ? (uint32_t)c : bin;
-        cnt = on ? h[c] : cnt;
-        acc += h[c];
-      }
-      bin = 8u * (uint32_t)src + (uint32_t)__builtin_amdgcn_readlane((int)bin, src);
-      above = (uint32_t)__builtin_amdgcn_readlane((int)above, src);
-      cnt = (uint32_t)__builtin_amdgcn_readlane((int)cnt, src);
-      const uint32_t lo = base + (bin << RW_SHIFT);
+    if (row_find_bin(bins, k, bin, above, cnt)) {
       // (the last bin has no upper end; one that starts at key 0 counts the
       // keys past the segment's end)
-      if (bin < RW_BINS - 1u && lo > 0u) {
-        if (above + cnt == k) return lo;
-        s.update(lo, above + cnt);
-        s.update(lo + (1u << RW_SHIFT), above);
-      }
+      lo = base + (bin << RW_SHIFT);
+      hi = (bin < RW_BINS - 1u) ? lo + (1u << RW_SHIFT) : hi;
+      cl = above + cnt;
+      split = lo == 0u;
+    } else {
+      hi = base;
     }
+    ch = above;
   }
+  bool once = true;
+  uint32_t wide = RW_WIDE;
   for (;;) {
-    for (;;) {
-      if (s.closed()) return s.lo;
-      const uint32_t near = (s.n < 5u) ? 3u : 6u;
-      const uint32_t up = k - s.ch, dn = (s.lo > 0u) ? s.cl - k : 0xFFFFFFFFu;
-      if (min(up, dn) > near) break;
-      uint32_t T, m = 0;
-      if (up <= dn) {
-        // the largest key below hi: differences wrap for those below
-        uint32_t best = 0u;
+    if (!split) {
+      if (cl == k || hi - lo <= unit) return lo;
+      // (k - ch is 1 at least; a bracket from 0 on gives up keys at its top only)
+      const uint32_t up = k - ch, dn = (lo > 0u) ? cl - k : 0xFFFFFFFFu;
+      split = min(up, dn) > 3u && !once;
+      once = false;
+      if (!split) {
+        uint32_t T, m = 0;
+        const bool top = up <= dn;
+        if (top) {
+          // the largest key below hi: differences wrap for those below
+          uint32_t best = 0u;
 #pragma unroll
-        for (int i = 0; i < V; ++i) best = max(best, key[i] - s.hi);
-        T = wave_uminmax<true>(best) + s.hi;
-        if (up == 1u) return T;
-      } else {
-        // the smallest key from lo on: differences wrap for those below
-        uint32_t best = 0xFFFFFFFFu;
+          for (int i = 0; i < V; ++i) best = max(best, key[i] - hi);
+          T = wave_uminmax<true>(best) + hi;
+          if (up == 1u) return T;
+        } else {
+          // the smallest key from lo on: differences wrap for those below
+          uint32_t best = 0xFFFFFFFFu;
 #pragma unroll
-        for (int i = 0; i < V; ++i) best = min(best, key[i] - s.lo);
-        T = wave_uminmax<false>(best) + s.lo;
+          for (int i = 0; i < V; ++i) best = min(best, key[i] - lo);
+          T = wave_uminmax<false>(best) + lo;
+        }
+#pragma unroll
+        for (int i = 0; i < V; ++i) m += (uint32_t)__popcll(__ballot(key[i] == T));
+        if (m > dn || (top && m >= up)) return T;
+        hi = top ? T : hi;
+        ch += top ? m : 0u;
+        lo = top ? lo : T + unit;
+        cl -= top ? 0u : m;
+        continue;
       }
-#pragma unroll
-      for (int i = 0; i < V; ++i) m += (uint32_t)__popcll(__ballot(key[i] == T));
-      const bool top = up <= dn;
-      if (m > dn || (top && m >= up)) return T;
-      if (!top && m == dn) return T + 1u;
-      s.hi = top ? T : s.hi;
-      s.ch += top ? m : 0u;
-      s.lo = top ? s.lo : T + (1u << tz);
-      s.cl -= top ? 0u : m;
     }
-    // a trial key: a lane counts its own keys and the lanes' counts are added
-    // once (the scalar unit would take a population count and an addition per key)
-    const uint32_t t = s.n ? s.next() : t0;
-    uint32_t under = 0;      // a bit per key below t
+    // ---- the bracket's keys into 512 bins, the zeros (and the keys past the
+    // segment's end) into none: 0 is T when the others do not reach its rank.
+    // A bracket from 0 on is tried in its 16 octaves at the top first.
+    uint32_t from = max(lo, unit);
+    const bool part = lo == 0u && hi - from > (1u << wide);
+    from = part ? hi - (1u << wide) : from;
+    const uint32_t w = hi - from, bits = 32u - (uint32_t)__builtin_clz((w - 1u) | 1u);
+    const uint32_t sh = max(tz, bits - min(bits, 9u));
+    clear();
 #pragma unroll
-    for (int i = 0; i < V; ++i) under = __builtin_amdgcn_alignbit(under, key[i] - t, 31);
-    const uint32_t c = (uint32_t)WAVE * V - wave_sum((uint32_t)__builtin_popcount(under));
-    if (c == k) return t;
-    s.update(t, c);
+    for (int i = 0; i < V; ++i) {
+      const uint32_t d = key[i] - from;
+      atomicAdd(&bins[d < w ? (int)(d >> sh) : below], 1u);
+    }
+    __builtin_amdgcn_wave_barrier();
+    split = !row_find_bin(bins, k - ch, bin, above, cnt);
+    if (split) {
+      if (!part) return 0u;
+      hi = from;
+      wide = 31u;
+    } else {
+      lo = from + (bin << sh);
+      hi = min(hi, lo + (1u << sh));
+      cl = ch + above + cnt;
+    }
+    ch += above;
   }
 }
 

@@ -99,6 +99,46 @@ def test_rows_aqsgd(tc, orc, L, dt, kind, off):
     assert tc.device_errors() == 0
 
 
+def ways(kind, L, dt, seed):
+    """rows that take each way through the threshold's search"""
+    g = torch.Generator().manual_seed(seed)
+    z = torch.randn((N, L), generator=g)
+    if kind == "gap":            # a tenth far above the rest: T on either side of it
+        z = torch.where(torch.rand((N, L), generator=g) < 0.1, z.sign() * (4 + z.abs()), z * 0.01)
+    elif kind == "sparse":       # few non-zero values
+        z = torch.where(torch.rand((N, L), generator=g) < 0.03, z, 0.0 * z)
+    elif kind == "far":          # the smaller half more than 16 octaves below the larger
+        z = torch.where(torch.rand((N, L), generator=g) < 0.5, z, z * 2.0 ** -20)
+    elif kind == "alike":        # one magnitude but for a few keys, zeros among them
+        z = torch.where(torch.rand((N, L), generator=g) < 0.02, z.round(), 1.5 * z.sign())
+    elif kind == "narrow":       # distinct values in one bin of the first window
+        z = 1.0 + torch.rand((N, L), generator=g) * 2.0 ** -9
+    return z.to(TORCH[dt])
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("kind", ["gap", "sparse", "far", "alike", "narrow"])
+@pytest.mark.parametrize("L", [5, 64, 255, 768, 2048])
+def test_rows_ways_through_the_search(tc, orc, L, kind, dt):
+    x = ways(kind, L, dt, 41)
+    for k in sorted({1, min(2, L), 3, -(-L // 50), -(-L // 10), -(-L // 8), -(-L * 45 // 100), -(-L * 6 // 10), L}):
+        e = np.zeros((N, L), np.float32)
+        ed = torch.zeros(N * L, device="cuda")
+        for step in range(2):
+            pl = tc.ef_step_topk(x.cuda(), ed, k, N)
+            torch.cuda.synchronize()
+            oi, ov, e = orc.ef_topk(raw(x), dt, e, N, L, k)
+            what = f"{N}x{L} {dt} {kind} k={k} step {step}"
+            assert_bits_equal(raw(pl.idx), oi, f"idx {what}")
+            assert_bits_equal(raw(pl.val), ov, f"val {what}")
+            assert_bits_equal(raw(ed).reshape(N, L), e, f"e {what}")
+        pl = tc.topk_compress(x.cuda(), k, N)
+        oi, ov = orc.topk_compress(raw(x), dt, N, L, k)
+        assert_bits_equal(raw(pl.idx), oi, f"plain idx {N}x{L} {dt} {kind} k={k}")
+        assert_bits_equal(raw(pl.val), ov, f"plain val {N}x{L} {dt} {kind} k={k}")
+    assert tc.device_errors() == 0
+
+
 def test_more_rows_than_resident(tc, orc):
     n, L, k = 9001, 65, 7
     x = make("normal", (n, L), "f32", 31)
