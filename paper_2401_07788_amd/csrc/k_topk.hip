@@ -485,7 +485,7 @@ __device__ __forceinline__ void copy_lds_skip2(uint32_t* __restrict__ di, T* __r
 // early are stored again by the caller.
 enum class Fine { FALLBACK, DONE, PLACE };
 
-template <typename InT, int SEL, int R, bool EARLY>
+template <typename InT, int SEL, int R, bool EARLY, bool LOOP>
 __device__ __forceinline__ Fine grp_fine(const TopkArgs& a, bool vec, uint64_t seg, uint32_t P, uint32_t part,
                                          const GrpMem& gm,
                                          GrpShared<(uint32_t)GRP_NT * R * (16 / sizeof(typename Elem<InT>::raw)),
@@ -499,8 +499,8 @@ __device__ __forceinline__ Fine grp_fine(const TopkArgs& a, bool vec, uint64_t s
   constexpr int NT = GRP_NT;
   constexpr int E = 16 / (int)sizeof(Raw);
   constexpr uint32_t CH = (uint32_t)NT * R * E;
-  const int t = (int)threadIdx.x;
-  const uint32_t dummy = (uint32_t)lane_id();
+  const int t = (int)grp_thread<LOOP>();
+  const uint32_t dummy = (uint32_t)t % WAVE;
   const uint32_t pre = A.prefix, lowb = 31u - A.pbits;   // key bits below the prefix
 
   // ---- per run: entries above or on the prefix, and on it (both < 2^16
@@ -614,8 +614,8 @@ __device__ __forceinline__ Fine grp_fine(const TopkArgs& a, bool vec, uint64_t s
 
   // words per thread for the group's size (16 workgroups each)
   bool ok;
-  if (P <= 64u) ok = grp_finish_b<NT, 4>(P, part, gm, sm, gs, A, sr);
-  else ok = grp_finish_b<NT, 16>(P, part, gm, sm, gs, A, sr);
+  if (P <= 64u) ok = grp_finish_b<NT, 4, LOOP>(P, part, gm, sm, gs, A, sr);
+  else ok = grp_finish_b<NT, 16, LOOP>(P, part, gm, sm, gs, A, sr);
   refresh(v);
   if (!ok) return Fine::FALLBACK;
   if (!early) {
@@ -702,7 +702,7 @@ __device__ __forceinline__ Fine grp_fine(const TopkArgs& a, bool vec, uint64_t s
 // aligned and segments start on 16-byte boundaries, so that whole runs move
 // as single 16-byte accesses; a run cut by the segment's end (or any run
 // without `vec`) goes element by element.
-template <typename InT, int SEL, int R>
+template <typename InT, int SEL, int R, bool LOOP>
 __device__ __forceinline__ void grp_segment(const TopkArgs& a, bool vec, uint64_t seg, uint32_t P,
                                             uint32_t part, const GrpMem& gm,
                                             GrpShared<(uint32_t)GRP_NT * R * (16 / sizeof(typename Elem<InT>::raw)),
@@ -713,8 +713,8 @@ __device__ __forceinline__ void grp_segment(const TopkArgs& a, bool vec, uint64_
   constexpr int NT = GRP_NT;
   constexpr int E = 16 / (int)sizeof(Raw);
   constexpr uint32_t CH = (uint32_t)NT * R * E;
-  const int t = (int)threadIdx.x;
-  const uint32_t dummy = (uint32_t)lane_id();
+  const int t = (int)grp_thread<LOOP>();
+  const uint32_t dummy = (uint32_t)t % WAVE;
   const uint64_t c0 = (uint64_t)part * CH;
   const Raw* xs = (const Raw*)a.x + seg * a.L + c0;
   float* es = (SEL == SEL_EF) ? a.e + seg * a.L + c0 : nullptr;
@@ -821,9 +821,10 @@ __device__ __forceinline__ void grp_segment(const TopkArgs& a, bool vec, uint64_
   }
 
   // ---- selection (elements past the segment's end hold +0: see grp_exchange_a)
-  // Staging ahead of exchange B needs registers of its own: with 16 or more
-  // fp32 values (and their residuals) per thread it would spill, so those
-  // layouts place once T is known.
+  // Staging ahead of exchange B needs registers of its own (more than there
+  // are with 16 or more fp32 values and their residuals per thread, when what
+  // the loop over segments shares stood in registers too): those layouts place
+  // once T is known.
   constexpr bool EARLY = !(sizeof(Raw) == 4 && R >= 4);
   SelResult sr;
   uint32_t ticket = 0;
@@ -834,13 +835,13 @@ __device__ __forceinline__ void grp_segment(const TopkArgs& a, bool vec, uint64_
     sr.T = 0x7FFFFFFFu; sr.r = 0; sr.gt_before = 0; sr.eq_before = 0;
   } else {
     const uint32_t n_loc = (uint32_t)min((uint64_t)CH, a.L - c0);
-    SelA A = grp_exchange_a<NT, R, E, CH>(v, zc, (uint32_t)a.k, n_loc, a.L, P, part, gm, sh.sel, sm, gs);
+    SelA A = grp_exchange_a<NT, R, E, CH, LOOP>(v, zc, (uint32_t)a.k, n_loc, a.L, P, part, gm, sh.sel, sm, gs);
     if (!A.fine) {
       grp_pass<NT, R, E>(v, 8u, 0u, P, gm, sh.sel, sm, gs, A);
       grp_clear_a(gm, gs.iter & 1u, P, part);
     }
     refresh(v);
-    const Fine f = grp_fine<InT, SEL, R, EARLY>(a, vec, seg, P, part, gm, sh, sm, gs, A, v, n, c0, ms, es, mlds, exiting, ticket, sr);
+    const Fine f = grp_fine<InT, SEL, R, EARLY, LOOP>(a, vec, seg, P, part, gm, sh, sm, gs, A, v, n, c0, ms, es, mlds, exiting, ticket, sr);
     if (f == Fine::DONE) {
       if (exiting) {
         grp_exit_finish<NT>(gm, P, gs, ticket, &sm.misc[0]);
@@ -999,11 +1000,11 @@ __global__ __launch_bounds__(GRP_NT) void k_topk_grp(TopkArgs a) {
   if (a.n_seg <= n_groups) {
     // one segment per group (a straight path: nothing for the compiler to
     // hoist out of a loop and keep in registers)
-    if (group < a.n_seg) grp_segment<InT, SEL, R>(a, vec, group, P, part, gm, sh, sm, gs, true, exited, mlds);
+    if (group < a.n_seg) grp_segment<InT, SEL, R, false>(a, vec, group, P, part, gm, sh, sm, gs, true, exited, mlds);
   } else {
     for (uint64_t seg = group; seg < a.n_seg; seg += n_groups, ++gs.iter) {
       const bool last_seg = seg + n_groups >= a.n_seg;
-      grp_segment<InT, SEL, R>(a, vec, seg, P, part, gm, sh, sm, gs, last_seg, exited, mlds);
+      grp_segment<InT, SEL, R, true>(a, vec, seg, P, part, gm, sh, sm, gs, last_seg, exited, mlds);
     }
   }
   if (P > 1 && !exited) {

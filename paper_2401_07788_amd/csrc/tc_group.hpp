@@ -159,6 +159,18 @@ __device__ __forceinline__ void block_excl_scan_multi(const uint32_t (&v)[R], ui
   __syncthreads();
 }
 
+// The thread's index.  In the loop over segments (LOOP) what follows from it is
+// computed where it is used: hoisted out of the loop it took all 256 registers
+// and, in the widest layouts, up to 50 more in scratch, where a straight path
+// needs about 140.  Two segments per group, AQ-SGD 30 %, 16 x 393,216: binary16
+// 49.1 -> 45.8 us, binary32 62.2 -> 54.1.
+template <bool LOOP>
+__device__ __forceinline__ uint32_t grp_thread() {
+  uint32_t t = threadIdx.x;
+  if constexpr (LOOP) asm volatile("" : "+v"(t));
+  return t;
+}
+
 // LDS of the group engine's selection
 template <uint32_t CLOC>
 struct GrpSelShared {
@@ -296,11 +308,11 @@ __device__ __forceinline__ void grp_find_merged(const uint32_t* gh, uint32_t k, 
 // the whole chunk it missed, and every segment whose length is not a multiple
 // of the chunk took the digit passes: 5 x 100,003 binary16, TopK 30 %, sender
 // 25.4 us).
-template <int NT, int R, int E, uint32_t CH>
+template <int NT, int R, int E, uint32_t CH, bool LOOP>
 __device__ __forceinline__ SelA grp_exchange_a(float (&v)[R][E], uint32_t zc, uint32_t k, uint32_t n_loc, uint64_t L,
                                                uint32_t P, uint32_t part, const GrpMem& g,
                                                GrpSelShared<grp_local_cap(CH)>& sh, GrpSmall& sm, GrpState& gs) {
-  const uint32_t t = threadIdx.x;
+  const uint32_t t = grp_thread<LOOP>();
   auto key = [&](int j, int i) { return mag_key(v[j][i]); };
   const uint32_t par = gs.iter & 1u;
   SelA A;
@@ -493,38 +505,48 @@ __device__ __forceinline__ void wave_find128(const uint32_t* h, uint32_t need, u
 }
 
 // Exchange B, second half: waits for the group, reads all records in one
-// round trip (SPT words per thread: up to 16 * SPT workgroups) and finds T,
-// the tie quota and the larger keys and ties of lower workgroups (the last
-// after one more barrier, by grp_finish_b_lower).  Returns false (nothing
+// round trip (SPT words per thread, two per access: up to 16 * SPT workgroups)
+// and finds T, the tie quota and the larger keys and ties of lower workgroups
+// (the last after one more barrier, by grp_finish_b_lower).  Returns false (nothing
 // decided) when some record could not hold its keys; the words of exchange A
 // (fine) or of the digit pass after it are cleared either way.
-template <int NT, int SPT>
+template <int NT, int SPT, bool LOOP>
 __device__ __forceinline__ bool grp_finish_b(uint32_t P, uint32_t part, const GrpMem& g, GrpSmall& sm, GrpState& gs,
                                              const SelA& A, SelResult& res) {
   constexpr int NW = NT / WAVE;
-  static_assert(REC_W * 2 == WAVE, "two records per wavefront read");
-  const uint32_t t = threadIdx.x, wv = t / WAVE, lane = (uint32_t)lane_id();
-  const uint32_t half = lane / REC_W, wi = lane % REC_W;
+  constexpr int LP = SPT / 2;                     // 8-byte loads per thread
+  constexpr uint32_t PERW = WAVE * 2 / REC_W;     // records per wavefront read
+  static_assert(WAVE * 2 % REC_W == 0, "whole records per wavefront read");
+  const uint32_t t = grp_thread<LOOP>(), wv = t / WAVE, lane = t % WAVE;
+  const uint32_t sub = lane / (REC_W / 2), wi = lane % (REC_W / 2);
   group_wait(g.ctl(), P * gs.nbar);
-  // lane i of wavefront wv reads word i % 32 of record 2 * (u*NW + wv) + i / 32
-  const uint32_t* rec = g.rec();
+  // lane i of wavefront wv reads words 2 (i % 16) and + 1 of record
+  // 4 * (u*NW + wv) + i / 16 (the last record again in place of one past it)
+  const uint64_t* rec = reinterpret_cast<const uint64_t*>(g.rec());
   uint32_t wd[SPT];
 #pragma unroll
-  for (int u = 0; u < SPT; ++u) {
-    const uint32_t w = 2u * (uint32_t)(u * NW + wv) + half;
-    wd[u] = (w < P) ? ld_agent(&rec[(uint64_t)w * REC_W + wi]) : 0u;
+  for (int u = 0; u < LP; ++u) {
+    const uint32_t w = PERW * (uint32_t)(u * NW + wv) + sub;
+    const uint64_t x = ld_agent64(&rec[min(w, P - 1u) * (REC_W / 2) + wi]);
+    wd[2 * u] = (uint32_t)x;
+    wd[2 * u + 1] = (uint32_t)(x >> 32);
   }
   if (A.fine) grp_clear_a(g, gs.iter & 1u, P, part);
   else grp_clear_pass(g, 0, P, part);
-  // headers (lanes 0 and 32) give the keys above the prefix before this
-  // workgroup; entries count into the histogram of their bits 13..7
+  // headers (the first word of a record) give the keys above the prefix before
+  // this workgroup; entries count into the histogram of their bits 13..7
   uint32_t abv = 0, bad = 0;
 #pragma unroll
+  for (int u = 0; u < LP; ++u) {
+    const uint32_t w = PERW * (uint32_t)(u * NW + wv) + sub;
+    const bool head = wi == 0u;
+    abv += (head && w < part) ? wd[2 * u] & 0xFFFFu : 0u;
+    bad |= head ? wd[2 * u] >> 16 : 0u;
+    wd[2 * u] = (head || w >= P) ? 0u : wd[2 * u];
+    wd[2 * u + 1] = (w >= P) ? 0u : wd[2 * u + 1];
+  }
+#pragma unroll
   for (int u = 0; u < SPT; ++u) {
-    const uint32_t w = 2u * (uint32_t)(u * NW + wv) + half;
-    abv += (wi == 0u && w < part) ? wd[u] & 0xFFFFu : 0u;
-    bad |= (wi == 0u) ? wd[u] >> 16 : 0u;
-    wd[u] = (wi == 0u) ? 0u : wd[u];
     const uint32_t c = wd[u] >> LOW_BITS;
     atomicAdd(&sm.h7a[c ? (wd[u] >> 7) & 0x7Fu : (uint32_t)LAST_BINS + lane], c);
   }
@@ -557,7 +579,7 @@ __device__ __forceinline__ bool grp_finish_b(uint32_t P, uint32_t part, const Gr
   uint32_t gt = 0, eq = 0;
 #pragma unroll
   for (int u = 0; u < SPT; ++u) {
-    const uint32_t w = 2u * (uint32_t)(u * NW + wv) + half;
+    const uint32_t w = PERW * (uint32_t)((u / 2) * NW + wv) + sub;
     const uint32_t c = (w < part) ? wd[u] >> LOW_BITS : 0u, kl = wd[u] & ((1u << LOW_BITS) - 1u);
     gt += (kl > low) ? c : 0u;
     eq += (kl == low) ? c : 0u;
