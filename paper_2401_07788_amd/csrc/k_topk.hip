@@ -539,9 +539,10 @@ __device__ __forceinline__ Fine grp_fine(const TopkArgs& a, bool vec, uint64_t s
   const bool direct = c_all <= REC_KEYS;          // workgroup-uniform
   const bool early = EARLY && c_all <= (uint32_t)WAVE;
   uint32_t run_key = ~0u, run_n = 0;              // equal keys in a row enter the table together
+  bool room = true;                               // until the table overflows (then the group falls back)
 #pragma unroll
   for (int j = 0; j < R; ++j) {
-    uint32_t cm = msk[j] >> 8;
+    uint32_t cm = room ? msk[j] >> 8 : 0u;
     if (cm) {
       uint32_t q = cb[j] + (ex[j] >> 16);
       const uint32_t sp0 = mb[j] + (ex[j] & 0xFFFFu), mm = msk[j] & 0xFFu;
@@ -558,7 +559,7 @@ __device__ __forceinline__ Fine grp_fine(const TopkArgs& a, bool vec, uint64_t s
         } else if (low == run_key) {
           ++run_n;
         } else {
-          if (run_n) grp_rle_add(sm, run_key, run_n);
+          if (run_n) room = grp_rle_add(sm, run_key, run_n);
           run_key = low;
           run_n = 1u;
         }
@@ -571,7 +572,7 @@ __device__ __forceinline__ Fine grp_fine(const TopkArgs& a, bool vec, uint64_t s
       } while (cm);
     }
   }
-  if (run_n) grp_rle_add(sm, run_key, run_n);
+  if (room && run_n) grp_rle_add(sm, run_key, run_n);
   grp_publish_b<NT>(part, gm, sm, gs, m_all - c_all, direct);
   refresh(v);
   // ---- while the group arrives: stage the entries above or on the prefix
@@ -851,7 +852,7 @@ __device__ __forceinline__ void grp_segment(const TopkArgs& a, bool vec, uint64_
       return;
     }
     if (f == Fine::FALLBACK)
-      sr = grp_fallback<NT, R, E, CH>(v, P, part, gm, sh.sel, sm, gs, A, A.fine ? 0u : 1u);
+      sr = grp_fallback<NT, R, E, CH, LOOP>(v, P, part, gm, sh.sel, sm, gs, A, A.fine ? 0u : 1u);
   }
   // the group's exchange words have all been read: draw the exit ticket now
   // (its answer is needed only at the end)

@@ -30,8 +30,8 @@
 // have once an example's activations repeat; or chunks that differ), one pass
 // over the next 8 bits, merged through device memory, gives a 20-bit prefix
 // for exchange B instead.  When too many distinct keys share the prefix, the
-// group goes on with digit passes of up to 8 bits and one exchange of
-// per-workgroup counts: exact for any input.
+// group goes on with a digit pass and one exchange of per-workgroup counts of
+// the last digit: exact for any input.
 #pragma once
 
 #include "tc_select.hpp"
@@ -49,6 +49,7 @@ constexpr uint32_t FINE_SLOTS = 128;      // fine counts kept for bins b1 mod 12
 constexpr uint32_t LOW_BITS = 19 - FINE_BITS;   // key bits below the fine prefix (at most that many in a record's entry)
 static_assert(LOW_BITS == 14 && LAST_BINS == 128, "two 7-bit digits below the fine prefix");
 constexpr uint32_t DIG_BINS = 256;        // digits of the fallback passes: up to 8 bits
+constexpr uint32_t CNT_BINS = 64, CNT_W = CNT_BINS + 1;   // last digit of the fallback: at most 6 bits
 constexpr uint32_t REC_P_MAX = 256;       // workgroups per segment of the record exchange
 constexpr uint32_t A_MARGIN = 16;         // bins added below the guessed one's neighbour (an octave)
 constexpr uint32_t RLE_SLOTS = 64;        // hash table of a workgroup's distinct keys on the prefix
@@ -65,7 +66,7 @@ __host__ __device__ constexpr uint32_t grp_local_cap(uint32_t CH) { return CH > 
 //   fine[2][128][32]      bits 18..14 of the keys in guessed bins, by bin mod 128
 //   hist2[4][256]         digit pass p: hist2(p)
 //   rec[P][32]            exchange B records
-//   cnt[P]                keys > T and == T per workgroup (fallback)
+//   cnt[P][65]            last digit's counts and keys above its prefix per workgroup (fallback)
 // The size keeps the words that earlier layouts used per workgroup (64 for
 // the record, 257 rows of digit slots): callers size their workspaces, and
 // the allocation-free entry point its refusals, by it.
@@ -78,6 +79,7 @@ static_assert(REC % 4 == 0, "records are 16-byte aligned");
 __host__ __device__ constexpr uint64_t grp_mem_words(uint32_t P) {
   return gm_off::REC + (uint64_t)P * 64u + 257ull * ((P + 7u) & ~7u);
 }
+static_assert(REC_W + CNT_W <= 64u + 257u, "records and counts fit");
 
 // the group's memory: one base pointer, pieces at fixed offsets
 struct GrpMem {
@@ -446,18 +448,23 @@ __device__ __forceinline__ void grp_clear_pass(const GrpMem& g, uint32_t p, uint
 
 // One of this workgroup's keys on the prefix (its low bits), c times, into
 // the table of distinct keys.  A table too full to place it raises misc[4]:
-// the record is then marked as overflowed.
-__device__ __forceinline__ void grp_rle_add(GrpSmall& sm, uint32_t low, uint32_t c) {
+// the record is then marked as overflowed.  False once that is so: what else
+// is on the prefix need not enter (up to 12,288 distinct keys, each of which
+// would try its eight places: 16 x 200,000 binary32 within 2^-9 of 1, TopK 10 %,
+// 131 us without this test and with one exchange more in the fallback, now 91).
+__device__ __forceinline__ bool grp_rle_add(GrpSmall& sm, uint32_t low, uint32_t c) {
+  if (__hip_atomic_load(&sm.misc[4], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0u) return false;
   uint32_t h = ((low * 0x9E5u) >> 4) & (RLE_SLOTS - 1u);
   for (uint32_t p = 0; p < RLE_PROBES; ++p) {
     const uint32_t old = atomicCAS(&sm.hk[h], 0u, low + 1u);
     if (old == 0u || old == low + 1u) {
       atomicAdd(&sm.hc[h], c);
-      return;
+      return true;
     }
     h = (h + 1u) & (RLE_SLOTS - 1u);
   }
   sm.misc[4] = 1u;
+  return false;
 }
 
 // Exchange B (fine mode), first half.  A record is a header (the keys above
@@ -599,49 +606,71 @@ __device__ __forceinline__ void grp_finish_b_lower(const GrpSmall& sm, SelResult
   for (int i = 0; i < NW; ++i) { res.gt_before += sm.scratch[i]; res.eq_before += sm.scratch[NW + i]; }
 }
 
-// The exact passes once a record overflowed: digit passes of up to 8 bits
-// merged through device memory until T is known, then one exchange of every
-// workgroup's counts of larger keys and ties, which gives what precedes this
-// workgroup.  `pass`: digit passes already done for this segment.
-template <int NT, int R, int E, uint32_t CH>
+// The exact passes once a record overflowed: a digit pass of 8 bits merged
+// through device memory, then the last bits (at most 6) counted per workgroup,
+// which also gives what precedes this workgroup.  `pass`: digit passes already
+// done for this segment.
+template <int NT, int R, int E, uint32_t CH, bool LOOP>
 __device__ __forceinline__ SelResult grp_fallback(float (&v)[R][E], uint32_t P, uint32_t part, const GrpMem& g,
                                                   GrpSelShared<grp_local_cap(CH)>& sh, GrpSmall& sm, GrpState& gs,
                                                   SelA A, uint32_t pass) {
-  const int t = (int)threadIdx.x;
-  auto key = [&](int j, int i) { return mag_key(v[j][i]); };
-  const uint32_t first = pass;
-  // at most three passes per segment, each with its own counts
-  for (; A.pbits < 31u; ++pass) {
-    grp_pass<NT, R, E>(v, min(8u, 31u - A.pbits), pass, P, g, sh, sm, gs, A);
-    if (pass > first) grp_clear_pass(g, pass - 1, P, part);
-  }
-  SelResult res;
-  res.T = A.prefix;
-  res.r = A.need;
-  // larger keys and ties of every workgroup (both below 2^16)
+  constexpr uint32_t NW = NT / WAVE;
+  const uint32_t t = grp_thread<LOOP>(), wv = t / WAVE, lane = t % WAVE;
+  grp_pass<NT, R, E>(v, 8u, pass, P, g, sh, sm, gs, A);
+  // ---- the last digit: this workgroup's counts, and its keys above the prefix
+  const uint32_t left = 31u - A.pbits;
+  dig_zero<NT>(sh.hist);
+  __syncthreads();
   refresh(v);
-  uint32_t ge = 0;
+  uint32_t gt = 0;
 #pragma unroll
   for (int j = 0; j < R; ++j)
 #pragma unroll
     for (int i = 0; i < E; ++i) {
-      const uint32_t kk = key(j, i);
-      ge += gt31(kk, res.T) | (eq31(kk, res.T) << 16);
+      const uint32_t kk = mag_key(v[j][i]), hi = kk >> left;
+      dig_add(sh.hist, hi == A.prefix, kk & ((1u << left) - 1u));
+      gt += gt31(hi, A.prefix);
     }
-  const uint32_t ge_wg = block_sum<NT>(ge, sm.scratch);
+  const uint32_t gt_wg = block_sum<NT>(gt, sm.scratch);   // (contains barriers)
+  dig_reduce<NT, CNT_BINS>(sh.hist, sm.red);
   uint32_t* cnt = g.cnt();
   gs.used_cnt = true;
-  if (t == 0) st_agent(&cnt[part], ge_wg);
+  if (t < CNT_BINS) st_agent(&cnt[part * CNT_W + t], sm.red[t]);
+  else if (t == CNT_BINS) st_agent(&cnt[part * CNT_W + t], gt_wg);
   group_sync(g.ctl(), P * ++gs.nbar);
-  uint32_t gt = 0, eq = 0;
-  for (uint32_t q = (uint32_t)t; q < part; q += NT) {
-    const uint32_t c = ld_agent(&cnt[q]);
-    gt += c & 0xFFFFu;
-    eq += c >> 16;
+  grp_clear_pass(g, pass, P, part);
+  // lane b of a wavefront adds up bin b of every eighth workgroup
+  static_assert(CNT_BINS == (uint32_t)WAVE, "a bin per lane");
+  uint32_t all = 0, bef = 0;
+#pragma unroll 4
+  for (uint32_t w = wv; w < P; w += NW) {
+    const uint32_t c = ld_agent(&cnt[w * CNT_W + lane]);
+    all += c;
+    bef += (w < part) ? c : 0u;
   }
-  grp_clear_pass(g, pass - 1, P, part);
-  res.gt_before = block_sum<NT>(gt, sm.scratch);
-  res.eq_before = block_sum<NT>(eq, sm.scratch);
+  uint32_t gtb = 0;
+  for (uint32_t w = t; w < part; w += NT) gtb += ld_agent(&cnt[w * CNT_W + CNT_BINS]);
+  sh.hist[(wv * 2u) * WAVE + lane] = all;
+  sh.hist[(wv * 2u + 1u) * WAVE + lane] = bef;
+  SelResult res;
+  res.gt_before = block_sum<NT>(gtb, sm.scratch);         // (contains barriers)
+  all = 0;
+  bef = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < NW; ++w) {
+    // (bins from the top: lane l takes bin 63 - l)
+    all += sh.hist[(w * 2u) * WAVE + (WAVE - 1u - lane)];
+    bef += sh.hist[(w * 2u + 1u) * WAVE + (WAVE - 1u - lane)];
+  }
+  const uint32_t incl = wave_incl_scan(all), bincl = wave_incl_scan(bef);
+  const uint64_t hit = __ballot(incl - all < A.need && A.need <= incl);
+  if (hit == 0 && t == 0) raise_error(KERR_INTERNAL);   // (the counts cover need: a hit is certain)
+  const int l = hit ? __builtin_ctzll(hit) : 0;
+  res.T = (A.prefix << left) | (WAVE - 1u - (uint32_t)l);
+  res.r = A.need - (uint32_t)__builtin_amdgcn_readlane((int)(incl - all), l);
+  res.gt_before += (uint32_t)__builtin_amdgcn_readlane((int)(bincl - bef), l);
+  res.eq_before = (uint32_t)__builtin_amdgcn_readlane((int)bef, l);
+  __syncthreads();
   return res;
 }
 
@@ -666,7 +695,7 @@ __device__ __forceinline__ void grp_exit_finish(const GrpMem& g, uint32_t P, con
   __syncthreads();
   if (!*flag) return;
   // the records and the counts lie back to back
-  const uint32_t n = P * REC_W + (gs.used_cnt ? P : 0u);
+  const uint32_t n = P * (REC_W + (gs.used_cnt ? CNT_W : 0u));
   uint32_t* rec = g.rec();
   for (uint32_t i = threadIdx.x; i < n; i += NT) st_agent(&rec[i], 0u);
   if (threadIdx.x == 0) {

@@ -99,6 +99,32 @@ def test_group_threshold_near_zero(tc, orc, L, dt, b):
     assert tc.device_errors() == 0
 
 
+@pytest.mark.parametrize("n_seg,L,dt", [(1, 40000, "f32"), (2, 300001, "f32"), (1, 3000000, "f32"), (20, 65000, "f32"),
+                                        (2, 300001, "bf16")])
+@pytest.mark.parametrize("spread", [2.0 ** -9, 2.0 ** -6])
+def test_group_records_overflow(tc, orc, n_seg, L, dt, spread):
+    """distinct keys on T's prefix in every workgroup, in some, and in none that
+    ranks before: with the prefix from the windows, and with one that a digit
+    pass gave (chunks of other magnitudes make the windows miss)"""
+    g = torch.Generator().manual_seed(19)
+    for miss in (False, True):
+        x = 1.0 + torch.rand((n_seg, L), generator=g) * spread
+        x[:, L // 2:L // 2 + L // 4] = 1.0 + spread / 3          # one key, many times
+        if miss:
+            x[:, :L // 5] *= 2.0 ** -8
+        x = x.to(TORCH[dt])
+        for k in (1, L // 10, L // 2, L * 7 // 8):
+            e = torch.zeros(n_seg * L, device="cuda")
+            pl = tc.ef_step_topk(x.cuda(), e, k, n_seg)
+            torch.cuda.synchronize()
+            oi, ov, oe = orc.ef_topk(raw(x), dt, torch.zeros(n_seg, L).numpy(), n_seg, L, k)
+            what = f"{n_seg}x{L} {dt} spread {spread} miss {miss} k={k}"
+            assert_bits_equal(raw(pl.idx), oi, f"idx {what}")
+            assert_bits_equal(raw(pl.val), ov, f"val {what}")
+            assert_bits_equal(raw(e).reshape(n_seg, L), oe, f"e {what}")
+    assert tc.device_errors() == 0
+
+
 def test_group_aqsgd_repeated_activations(tc, orc):
     """the same two activations in turn: after a few visits the changes have a
     gap around the threshold, repeat in few values, or are all zero"""
