@@ -37,7 +37,7 @@ namespace tc {
 // that the group's cross-workgroup traffic stays behind one L2.
 __device__ __forceinline__ void map_wg(uint32_t wg, uint32_t grid, uint32_t P, uint32_t& group,
                                        uint32_t& part) {
-  if (P > 1 && grid % (8u * P) == 0u) {
+  if (grid % (8u * P) == 0u) {
     const uint32_t xcd = wg & 7u, q = wg >> 3;
     group = xcd + 8u * (q / P);
     part = q % P;
@@ -307,13 +307,13 @@ __global__ __launch_bounds__(WAVE) void k_topk_row(TopkArgs a) {
 }
 
 // ----------------------------------------------------------- group engine
-// LDS: the selection's histogram and candidate list, then (after the
-// selection) the workgroup's payload entries, staged so that they leave in
-// index order with full-line stores; WAVE extra entries are per-lane dummy
-// slots for the entries a lane does not keep.
+// LDS: the selection's histogram, then (after the selection) the workgroup's
+// payload entries, staged so that they leave in index order with full-line
+// stores; WAVE extra entries are per-lane dummy slots for the entries a lane
+// does not keep.
 template <uint32_t CH, typename Raw>
 union GrpShared {
-  GrpSelShared<grp_local_cap(CH)> sel;
+  GrpSelShared sel;
   struct {
     uint32_t idx[CH + WAVE];
     Raw val[CH + WAVE];
@@ -836,7 +836,7 @@ __device__ __forceinline__ void grp_segment(const TopkArgs& a, bool vec, uint64_
     sr.T = 0x7FFFFFFFu; sr.r = 0; sr.gt_before = 0; sr.eq_before = 0;
   } else {
     const uint32_t n_loc = (uint32_t)min((uint64_t)CH, a.L - c0);
-    SelA A = grp_exchange_a<NT, R, E, CH, LOOP>(v, zc, (uint32_t)a.k, n_loc, a.L, P, part, gm, sh.sel, sm, gs);
+    SelA A = grp_exchange_a<NT, R, E, LOOP>(v, zc, (uint32_t)a.k, n_loc, a.L, P, part, gm, sh.sel, sm, gs);
     if (!A.fine) {
       grp_pass<NT, R, E>(v, 8u, 0u, P, gm, sh.sel, sm, gs, A);
       grp_clear_a(gm, gs.iter & 1u, P, part);
@@ -852,7 +852,7 @@ __device__ __forceinline__ void grp_segment(const TopkArgs& a, bool vec, uint64_
       return;
     }
     if (f == Fine::FALLBACK)
-      sr = grp_fallback<NT, R, E, CH, LOOP>(v, P, part, gm, sh.sel, sm, gs, A, A.fine ? 0u : 1u);
+      sr = grp_fallback<NT, R, E, LOOP>(v, P, part, gm, sh.sel, sm, gs, A, A.fine ? 0u : 1u);
   }
   // the group's exchange words have all been read: draw the exit ticket now
   // (its answer is needed only at the end)
@@ -989,8 +989,7 @@ __global__ __launch_bounds__(GRP_NT) void k_topk_grp(TopkArgs a) {
   uint32_t group, part;
   map_wg(blockIdx.x, gridDim.x, P, group, part);
   const uint32_t n_groups = gridDim.x / P;
-  GrpMem gm{};
-  if (P > 1) gm = grp_mem(a.ws, group, P);
+  const GrpMem gm = grp_mem(a.ws, group, P);
   GrpState gs;
   bool exited = false;
   // whole 16-byte runs everywhere: every buffer 16-byte aligned, segment
@@ -1008,7 +1007,7 @@ __global__ __launch_bounds__(GRP_NT) void k_topk_grp(TopkArgs a) {
       grp_segment<InT, SEL, R, true>(a, vec, seg, P, part, gm, sh, sm, gs, last_seg, exited, mlds);
     }
   }
-  if (P > 1 && !exited) {
+  if (!exited) {
     const uint32_t ticket = grp_exit_ticket(gm);
     grp_exit_finish<GRP_NT>(gm, P, gs, ticket, &sm.misc[0]);
   }
@@ -1590,7 +1589,7 @@ GrpFill grp_fill(int dt, uint64_t n_seg, uint64_t L) {
     f.P = (L + ch - 1) / ch;
     if (n_seg * f.P >= cus) break;
   }
-  if (f.P > GRP_MAX_P) return f;
+  if (f.P > cus) return f;   // (never resident at once)
   uint64_t groups = std::min<uint64_t>(n_seg, std::max<uint64_t>(1, cus / f.P));
   if (groups >= 8) groups -= groups % 8;
   // sized for the most groups any instance could keep resident (4 workgroups

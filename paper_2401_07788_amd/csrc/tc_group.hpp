@@ -39,7 +39,6 @@
 namespace tc {
 
 constexpr int GRP_NT = 512;
-constexpr uint32_t GRP_MAX_P = 1024;      // workgroups per segment the engine supports
 constexpr uint32_t REC_W = 32;            // words per record: header, then distinct keys
 constexpr uint32_t REC_KEYS = REC_W - 1;
 constexpr uint32_t REC_OVF = 0xFFu;       // header: more distinct keys than a record holds
@@ -54,9 +53,6 @@ constexpr uint32_t REC_P_MAX = 256;       // workgroups per segment of the recor
 constexpr uint32_t A_MARGIN = 16;         // bins added below the guessed one's neighbour (an octave)
 constexpr uint32_t RLE_SLOTS = 64;        // hash table of a workgroup's distinct keys on the prefix
 constexpr uint32_t RLE_PROBES = 8;
-
-// candidate keys the LDS list holds (records of up to 64 workgroups)
-__host__ __device__ constexpr uint32_t grp_local_cap(uint32_t CH) { return CH > 4096u ? CH : 4096u; }
 
 // Device memory owned by one group (inside the caller's workspace; zero on
 // entry and left zero on exit), as word offsets from the group's base:
@@ -174,10 +170,8 @@ __device__ __forceinline__ uint32_t grp_thread() {
 }
 
 // LDS of the group engine's selection
-template <uint32_t CLOC>
 struct GrpSelShared {
   uint32_t hist[HIST_BINS + WAVE];   // histograms (the last WAVE words: per-lane dummies)
-  uint32_t cand[CLOC];               // exchange B records of all workgroups
 };
 
 struct GrpSmall {
@@ -253,8 +247,8 @@ __device__ __forceinline__ void grp_clear_a(const GrpMem& g, uint32_t par, uint3
 // counters of both exchanges, cleared before the workgroup's values arrive,
 // so that the keys of each run can be counted as soon as that run's loads
 // land.
-template <int NT, typename SH>
-__device__ __forceinline__ void grp_hist_clear(SH& sh, GrpSmall& sm) {
+template <int NT>
+__device__ __forceinline__ void grp_hist_clear(GrpSelShared& sh, GrpSmall& sm) {
   zero_lds<NT>(sh.hist, HIST_BINS);
   const uint32_t t = threadIdx.x;
   static_assert(NT >= 2 * LAST_BINS + 2 * (int)RLE_SLOTS + (int)REC_W && NT >= 3 * (int)FINE_N, "one word per thread");
@@ -270,8 +264,7 @@ __device__ __forceinline__ void grp_hist_clear(SH& sh, GrpSmall& sm) {
 // One key into it; exact zeros (common after a ReLU, and the padding) are
 // counted in the thread's zc and added once per wave by exchange A, off one
 // hot bin.
-template <typename SH>
-__device__ __forceinline__ void grp_hist_add(SH& sh, uint32_t kk, uint32_t& zc) {
+__device__ __forceinline__ void grp_hist_add(GrpSelShared& sh, uint32_t kk, uint32_t& zc) {
   const uint32_t z = eq31(kk, 0u);
   zc += z;
   atomicAdd(&sh.hist[pick(z, HIST_BINS + (uint32_t)lane_id(), kk >> 19)], 1u);
@@ -298,7 +291,7 @@ __device__ __forceinline__ void grp_find_merged(const uint32_t* gh, uint32_t k, 
   find_bin_loc<NT, BPT>(loc, k, scratch, found);
 }
 
-// Exchange A for one segment held by the P > 1 workgroups of a group (this
+// Exchange A for one segment held by the P workgroups of a group (this
 // one is `part`, with n_loc >= 1 elements of the segment), k >= 1; every key
 // of the workgroup is in the first histogram (grp_hist_clear, then
 // grp_hist_add per key; zc: this thread's exact zeros).  v[j][i] is element i
@@ -310,10 +303,10 @@ __device__ __forceinline__ void grp_find_merged(const uint32_t* gh, uint32_t k, 
 // the whole chunk it missed, and every segment whose length is not a multiple
 // of the chunk took the digit passes: 5 x 100,003 binary16, TopK 30 %, sender
 // 25.4 us).
-template <int NT, int R, int E, uint32_t CH, bool LOOP>
+template <int NT, int R, int E, bool LOOP>
 __device__ __forceinline__ SelA grp_exchange_a(float (&v)[R][E], uint32_t zc, uint32_t k, uint32_t n_loc, uint64_t L,
                                                uint32_t P, uint32_t part, const GrpMem& g,
-                                               GrpSelShared<grp_local_cap(CH)>& sh, GrpSmall& sm, GrpState& gs) {
+                                               GrpSelShared& sh, GrpSmall& sm, GrpState& gs) {
   const uint32_t t = grp_thread<LOOP>();
   auto key = [&](int j, int i) { return mag_key(v[j][i]); };
   const uint32_t par = gs.iter & 1u;
@@ -410,8 +403,8 @@ __device__ __forceinline__ SelA grp_exchange_a(float (&v)[R][E], uint32_t zc, ui
 // One digit pass (pass p of the segment): the next w <= 8 bits of the keys
 // that share the known prefix, counted by every workgroup and merged through
 // hist2(p).
-template <int NT, int R, int E, typename SH>
-__device__ __forceinline__ void grp_pass(float (&v)[R][E], uint32_t w, uint32_t p, uint32_t P, const GrpMem& g, SH& sh,
+template <int NT, int R, int E>
+__device__ __forceinline__ void grp_pass(float (&v)[R][E], uint32_t w, uint32_t p, uint32_t P, const GrpMem& g, GrpSelShared& sh,
                                          GrpSmall& sm, GrpState& gs, SelA& A) {
   const int t = (int)threadIdx.x;
   const uint32_t left = 31u - A.pbits, shift = left - w;
@@ -610,9 +603,9 @@ __device__ __forceinline__ void grp_finish_b_lower(const GrpSmall& sm, SelResult
 // through device memory, then the last bits (at most 6) counted per workgroup,
 // which also gives what precedes this workgroup.  `pass`: digit passes already
 // done for this segment.
-template <int NT, int R, int E, uint32_t CH, bool LOOP>
+template <int NT, int R, int E, bool LOOP>
 __device__ __forceinline__ SelResult grp_fallback(float (&v)[R][E], uint32_t P, uint32_t part, const GrpMem& g,
-                                                  GrpSelShared<grp_local_cap(CH)>& sh, GrpSmall& sm, GrpState& gs,
+                                                  GrpSelShared& sh, GrpSmall& sm, GrpState& gs,
                                                   SelA A, uint32_t pass) {
   constexpr uint32_t NW = NT / WAVE;
   const uint32_t t = grp_thread<LOOP>(), wv = t / WAVE, lane = t % WAVE;
