@@ -9,6 +9,7 @@ library is missing or no GPU is present, the calls raise.
 from __future__ import annotations
 
 import ctypes as C
+import operator
 import os
 import threading
 from typing import NamedTuple, Optional
@@ -223,6 +224,10 @@ _PLANS_MAX = 1024
 
 
 def _plan(kind: int, device, n_seg: int, seg_len: int, k: int = 0, bits: int = 0, wire: int = TC_F32) -> _Plan:
+    # plans are found by plain ints: a float that equals one is refused whatever
+    # is cached, and other integers (numpy's, a tensor's) are not kept
+    if not (type(n_seg) is type(seg_len) is type(k) is type(bits) is int):
+        n_seg, seg_len, k, bits = (int(operator.index(v)) for v in (n_seg, seg_len, k, bits))
     key = (kind, device.index, n_seg, seg_len, k, bits, wire)
     p = _plans.get(key)
     if p is None:

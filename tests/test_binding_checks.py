@@ -3,6 +3,7 @@ before anything reaches the C ABI: the library sees only pointers, so a
 payload made for another k or segment count would otherwise let a kernel
 write past its arrays.  These checks run on the CPU (they come before the
 binding asks for GPU tensors)."""
+import numpy as np
 import pytest
 import torch
 
@@ -109,3 +110,20 @@ def test_efmix_rejects_foreign_payloads():
         tc.efmix_step(x, e, 41, 2, out=(good[0], payload(2, ke + 1, 4096, torch.float32)))
     with pytest.raises(ValueError, match="budget"):
         tc.efmix_reconstruct(good[0], payload(2, ke - 1, 4096, torch.float32), 4096)
+
+
+def test_counts_are_whole_numbers_whatever_was_called_before():
+    """the plan of a shape is shared by its calls: a float equal to an int, which
+    would find the int's plan, is refused as before, and a plan is found by
+    numbers alone (a tensor that holds one is not kept)"""
+    x = torch.zeros((4, 64), dtype=torch.float16)
+    for _ in range(2):
+        with pytest.raises(ValueError, match="GPU"):
+            tc.topk_compress(x, 3, 4, out=payload(4, 3, 64))
+        with pytest.raises(TypeError, match="integer"):
+            tc.topk_compress(x, 3.0, 4, out=payload(4, 3, 64))
+        with pytest.raises(TypeError, match="integer"):
+            tc.topk_compress(x, 3, 4.0, out=payload(4, 3, 64))
+    same = tc._plan(tc.TC_TOPK, x.device, 4, 64, 3)
+    assert tc._plan(tc.TC_TOPK, x.device, np.int64(4), 64, torch.tensor(3)) is same
+    assert all(type(v) is int or v is None for key in tc._plans for v in key)
