@@ -46,6 +46,10 @@
  *             are sized to fit the device at once, and their waits are
  *             bounded (TC_KERR_TIMEOUT), but two of them should not share the
  *             device with other long-running kernels on concurrent streams.
+ *             They are the senders of TopK segments of 32,769 elements up to
+ *             what one resident group holds (up to 256 workgroups, 3,145,728
+ *             elements) and of quantization groups of more than 16,384
+ *             elements; the others' workgroups do not wait.
  *             Once TC_KERR_TIMEOUT is set on a device, every later such
  *             kernel gives up its waits early and its results are invalid
  *             until tc_device_errors(..., clear = 1) resets the bit and the
